@@ -3,6 +3,7 @@
 // The declarations and their contracts are in include/kvx.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
@@ -54,7 +55,7 @@ struct kvx_plan {
   int32_t* layer_map = nullptr;  // [Lt*mix]
   double* fs = nullptr;          // [Ds/2] theta_i / 2pi (zeros when RoPE is off)
   double* ft = nullptr;          // [Dt/2]
-  void* w[2] = {nullptr, nullptr};  // tiled: [Lt][dout][din]; fused: packed fragments
+  void* w[2] = {nullptr, nullptr};  // packed fragments (pack_tiled; fused kernel: fused_feature_of_slot)
   void* wh[2] = {nullptr, nullptr}; // fused, precision F16: packed fp16 fragments
   float* bias[2] = {nullptr, nullptr};
   // fused kernel: a zero area that lanes without data load from, and an area
@@ -103,27 +104,87 @@ bool fused_supported(const kvx_plan& p) {
          int64_t(p.tgt.n_layers) * p.mix <= kMaxLayerMap;
 }
 
-// Target rows per workgroup of the tiled kernel, and the LDS its pooled rows
-// take (rows x din fp32).
-int tiled_rows(int din) {
-  int r = 16384 / (din > 0 ? din : 1);
-  return r < 1 ? 1 : (r > 16 ? 16 : r);
+// Contractions the general kernel takes.
+constexpr int kMaxTiledDin = 16384;
+
+// Pair blocks (32 output RoPE pairs) and chunks (64 input RoPE pairs) of the
+// general kernel, the last of each zero-padded.
+int tiled_npb(int64_t dout) { return static_cast<int>((dout / 2 + 31) / 32); }
+int tiled_nch(int64_t din) { return static_cast<int>((din / 2 + 63) / 64); }
+
+// General kernel's weights W [Lt][dout][din] as the fragments its waves load:
+// per (layer, pair block, group of 8 slots, member) the 64 lanes' 4 slots;
+// lane n holds output pair 32 pb + n % 32 at slots 8 q + 4 (n / 32) .. +3.
+// Slot s of chunk c is pair 64 c + s % 64 of the flattened (mixed layer, head,
+// d < Ds/2) list, member s / 64; slots and outputs past the last pair are
+// zero.  One thread per (group, member, lane) piece; grid-stride.
+template <typename T>
+__global__ void __launch_bounds__(256) pack_tiled(const T* w, T* out, int lt, int din, int dout,
+                                                  int ds, int dt, int npb, int qn) {
+  const int64_t total = static_cast<int64_t>(lt) * npb * qn * 128;
+  const int hs = ds / 2, ht = dt / 2;
+  for (int64_t idx = blockIdx.x * 256ll + threadIdx.x; idx < total; idx += gridDim.x * 256ll) {
+    const int n = idx % 64, m = idx / 64 % 2, q = idx / 128 % qn;
+    const int64_t rest = idx / 128 / qn;
+    const int pb = rest % npb;
+    const int64_t l = rest / npb;
+    const int p = 32 * pb + n % 32;
+    T v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int s = 8 * q + 4 * (n / 32) + e;
+      const int pair = 64 * (s / 128) + s % 64;
+      const bool ok = p < dout / 2 && pair < din / 2;
+      const int64_t o = p / ht * dt + p % ht + m * ht;
+      const int64_t i = pair / hs * ds + pair % hs + (s % 128 >= 64 ? hs : 0);
+      v[e] = ok ? w[(l * dout + o) * din + i] : T(0);
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) out[idx * 4 + e] = v[e];
+  }
 }
-// dynamic LDS a launch gets without raising the kernel's limit (64 KiB):
-// din <= 16384
-constexpr size_t kMaxLdsBytes = 64 * 1024;
-size_t tiled_lds_bytes(int din) { return size_t(tiled_rows(din)) * din * sizeof(float); }
 
 // Input feature held in K-slot `k` of the fused kernel: chunk c = k / 128 holds
 // the RoPE pairs 64c .. 64c+63 of the flattened (mixed layer, head, d < Ds/2)
 // list, first members in slots 0..63, second members (d + Ds/2) in 64..127.
-int64_t fused_feature_of_slot(int64_t k, int64_t ds) {
+__host__ __device__ int64_t fused_feature_of_slot(int64_t k, int64_t ds) {
   const int64_t c = k / 128, s = k % 128;
   const int64_t pair = 64 * c + (s % 64);
   const int64_t half = ds / 2;
   const int64_t head = pair / half;  // (j * Hs + h)
   const int64_t d = pair % half + (s >= 64 ? half : 0);
   return head * ds + d;
+}
+
+// Fused kernel's weights: fragment (layer, feature block nb, k-step ks) of
+// v_mfma_f32_32x32x16_bf16, lane holds W[nb*32 + lane%32][feature of slot
+// ks*16 + 8*(lane/32) + j], j < 8 -- 8 consecutive features of one head
+// member, Ds being a multiple of 16.  `h`, when given, receives the same
+// fragments as fp16 (exact in fp16's normal range, smaller magnitudes round to
+// the nearest subnormal); a weight outside the fp16 range sets *bad.  One
+// thread per lane's piece; grid-stride.
+__global__ void __launch_bounds__(256) pack_fused(const uint16_t* w, uint16_t* out, uint16_t* h,
+                                                  int32_t* bad, int lt, int din, int dout, int ds) {
+  const int ksn = din / 16, nbn = dout / 32;
+  const int64_t total = static_cast<int64_t>(lt) * nbn * ksn * 64;
+  for (int64_t idx = blockIdx.x * 256ll + threadIdx.x; idx < total; idx += gridDim.x * 256ll) {
+    const int n = idx % 64, ks = idx / 64 % ksn;
+    const int64_t row = idx / 64 / ksn * 32 + n % 32;  // (layer, output)
+    const uint16_t* p = w + row * din + fused_feature_of_slot(ks * 16 + 8 * (n / 32), ds);
+    uint16_t v[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = p[j];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) out[idx * 8 + j] = v[j];
+    if (h) {
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const float f = bf16_to_f32(v[j]);
+        if (!(fabsf(f) <= 65504.0f)) *bad = 1;
+        h[idx * 8 + j] = __builtin_bit_cast(uint16_t, static_cast<_Float16>(f));
+      }
+    }
+  }
 }
 
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -180,8 +241,7 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   p->din = static_cast<int32_t>(din64);
   p->dout = static_cast<int32_t>(dout64);
   p->kernel = fused_supported(*p) ? kFused : kTiled;
-  // the tiled kernel holds one pooled row (din fp32) per target row in LDS
-  if (p->kernel == kTiled && tiled_lds_bytes(p->din) > kMaxLdsBytes) {
+  if (p->kernel == kTiled && p->din > kMaxTiledDin) {
     delete p;
     return KVX_EUNSUPPORTED;
   }
@@ -198,15 +258,18 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   if (e != hipSuccess) return fail(hip_fail(e));
 
   const size_t esz = d->dtype == KVX_F32 ? 4 : 2;
-  const size_t wbytes = size_t(lt) * dout64 * din64 * esz;
+  // packed elements per layer (general kernel: pair blocks and chunks padded)
+  const size_t pelems = p->kernel == kFused ? size_t(dout64) * din64
+                                            : size_t(tiled_npb(dout64)) * tiled_nch(din64) * 64 * kGSlots;
+  const size_t pbytes = size_t(lt) * pelems * esz;
   const size_t bbytes = size_t(lt) * dout64 * sizeof(float);
   const size_t mbytes = size_t(lt) * d->mix * sizeof(int32_t);
   const size_t fsb = d->src.head_dim / 2 * sizeof(double);
   const size_t ftb = d->tgt.head_dim / 2 * sizeof(double);
   const bool want_f16 = p->kernel == kFused && d->precision == KVX_PREC_F16;
-  const size_t hbytes = want_f16 ? wbytes : 0;
-  size_t off_w0 = 0, off_w1 = align256(wbytes);
-  size_t off_h0 = off_w1 + align256(wbytes), off_h1 = off_h0 + align256(hbytes);
+  const size_t hbytes = want_f16 ? pbytes : 0;
+  size_t off_w0 = 0, off_w1 = align256(pbytes);
+  size_t off_h0 = off_w1 + align256(pbytes), off_h1 = off_h0 + align256(hbytes);
   size_t off_b0 = off_h1 + align256(hbytes);
   size_t off_b1 = off_b0 + align256(bbytes), off_m = off_b1 + align256(bbytes);
   size_t off_fs = off_m + align256(mbytes), off_ft = off_fs + align256(fsb);
@@ -237,53 +300,35 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   e = hipMemset(p->zsink, 0, kSinkBytes);
   if (e != hipSuccess) return fail(hip_fail(e));
 
-  // Weights: copy to the host, repack, upload.  Plan creation is once per
-  // translator, so clarity wins over speed here.
-  std::vector<char> host(wbytes), packed;
+  // Weights: packed on the device, straight from the caller's buffers (the
+  // trash area serves as the fp16 range flag until the plan is used).
+  int32_t* bad = static_cast<int32_t*>(p->trash);
+  e = hipMemset(bad, 0, sizeof *bad);
+  if (e != hipSuccess) return fail(hip_fail(e));
   const void* wsrc[2] = {d->w_k, d->w_v};
+  const dim3 pgrid(static_cast<unsigned>(std::min<size_t>(8192, (size_t(lt) * pelems / 4 + 255) / 256)));
   for (int kv = 0; kv < 2; ++kv) {
-    e = hipMemcpy(host.data(), wsrc[kv], wbytes, hipMemcpyDeviceToHost);
+    if (p->kernel == kFused)
+      pack_fused<<<pgrid, dim3(256)>>>(static_cast<const uint16_t*>(wsrc[kv]),
+                                       static_cast<uint16_t*>(p->w[kv]),
+                                       static_cast<uint16_t*>(p->wh[kv]), bad, int(lt), p->din,
+                                       p->dout, d->src.head_dim);
+    else if (esz == 4)
+      pack_tiled<float><<<pgrid, dim3(256)>>>(
+          static_cast<const float*>(wsrc[kv]), static_cast<float*>(p->w[kv]), int(lt), p->din,
+          p->dout, d->src.head_dim, d->tgt.head_dim, tiled_npb(dout64), tiled_nch(din64) * kGQ);
+    else
+      pack_tiled<bf16_t><<<pgrid, dim3(256)>>>(
+          static_cast<const bf16_t*>(wsrc[kv]), static_cast<bf16_t*>(p->w[kv]), int(lt), p->din,
+          p->dout, d->src.head_dim, d->tgt.head_dim, tiled_npb(dout64), tiled_nch(din64) * kGQ);
+    e = hipGetLastError();
     if (e != hipSuccess) return fail(hip_fail(e));
-    const void* up = host.data();
-    if (p->kernel == kFused) {
-      // A fragment (feature block nb, k-step ks) of v_mfma_f32_32x32x16_bf16:
-      // lane holds W[nb*32 + lane%32][feature of slot ks*16 + 8*(lane/32) + j].
-      packed.resize(wbytes);
-      const uint16_t* wsrc16 = reinterpret_cast<const uint16_t*>(host.data());
-      uint16_t* dst = reinterpret_cast<uint16_t*>(packed.data());
-      const int64_t nb_n = dout64 / 32, ks_n = din64 / 16;
-      std::vector<int64_t> feat(din64);
-      for (int64_t k = 0; k < din64; ++k) feat[k] = fused_feature_of_slot(k, d->src.head_dim);
-      for (int64_t l = 0; l < lt; ++l)
-        for (int64_t nb = 0; nb < nb_n; ++nb)
-          for (int64_t ks = 0; ks < ks_n; ++ks)
-            for (int lanei = 0; lanei < 64; ++lanei)
-              for (int jj = 0; jj < 8; ++jj) {
-                const int64_t o = nb * 32 + lanei % 32;
-                const int64_t i = feat[ks * 16 + 8 * (lanei / 32) + jj];
-                dst[((((l * nb_n + nb) * ks_n + ks) * 64 + lanei) * 8) + jj] =
-                    wsrc16[(l * dout64 + o) * din64 + i];
-              }
-      up = packed.data();
-    }
-    e = hipMemcpy(p->w[kv], up, wbytes, hipMemcpyHostToDevice);
+  }
+  if (want_f16) {
+    int32_t hb = 0;
+    e = hipMemcpy(&hb, bad, sizeof hb, hipMemcpyDeviceToHost);
     if (e != hipSuccess) return fail(hip_fail(e));
-    if (want_f16) {
-      // the same fragments as fp16 (exact for bf16 values in the fp16 normal
-      // range; smaller magnitudes round to the nearest fp16 subnormal)
-      std::vector<uint16_t> h(wbytes / 2);
-      const uint16_t* src16 = static_cast<const uint16_t*>(up);
-      for (size_t i = 0; i < h.size(); ++i) {
-        uint32_t u = static_cast<uint32_t>(src16[i]) << 16;
-        float f;
-        std::memcpy(&f, &u, sizeof f);
-        if (!(std::fabs(f) <= 65504.0f)) return fail(KVX_EUNSUPPORTED);
-        _Float16 hv = static_cast<_Float16>(f);
-        std::memcpy(&h[i], &hv, sizeof hv);
-      }
-      e = hipMemcpy(p->wh[kv], h.data(), wbytes, hipMemcpyHostToDevice);
-      if (e != hipSuccess) return fail(hip_fail(e));
-    }
+    if (hb) return fail(KVX_EUNSUPPORTED);
   }
   const float* bsrc[2] = {d->b_k, d->b_v};
   for (int kv = 0; kv < 2; ++kv) {
@@ -360,6 +405,50 @@ void launch_fused(bool identity, bool ds128, int precision, int grid, hipStream_
     case KVX_PREC_F16: launch_fused_f16(identity, ds128, grid, st, a); break;
     default: launch_fused_bf16x2(identity, ds128, grid, st, a); break;
   }
+}
+
+// The general kernel for one group of contexts.
+template <typename T>
+void launch_tiled(const kvx_plan* p, const Strides& ss, const Strides& ts, const char* sk,
+                  const char* sv, char* tk, char* tv, const kvx_io& io, bool identity,
+                  const Paging& pg, const BatchArgs& ba, int tiles, hipStream_t st) {
+  TiledArgs<T> a{};
+  a.src[0] = reinterpret_cast<const T*>(sk);
+  a.src[1] = reinterpret_cast<const T*>(sv);
+  a.ss = ss;
+  a.tgt[0] = reinterpret_cast<T*>(tk);
+  a.tgt[1] = reinterpret_cast<T*>(tv);
+  a.ts = ts;
+  for (int kv = 0; kv < 2; ++kv) {
+    a.w[kv] = static_cast<const T*>(p->w[kv]);
+    a.bias[kv] = p->bias[kv];
+  }
+  a.layer_map = p->layer_map;
+  a.mix = p->mix;
+  a.hs = p->src.n_kv_heads;
+  a.ds = p->src.head_dim;
+  a.ht = p->tgt.n_kv_heads;
+  a.dt = p->tgt.head_dim;
+  a.din = p->din;
+  a.dout = p->dout;
+  a.fs = p->fs;
+  a.ft = p->ft;
+  a.row_ptr = io.row_ptr;
+  a.col_idx = io.col_idx;
+  a.weight = io.weight;
+  a.identity = identity;
+  a.row_tiles = tiles;
+  a.npb = tiled_npb(p->dout);
+  a.nch = tiled_nch(p->din);
+  a.pg = pg;
+  a.ba = ba;
+  // Four pair blocks per workgroup share one gather of its rows; one each
+  // (the four waves then split the contraction) while the larger groups would
+  // leave compute units idle.
+  const int64_t units = int64_t(tiles) * p->tgt.n_layers * 2;
+  a.group = units * tiled_ntiles(a.npb, 4) < p->n_cu ? 1 : 4;
+  const dim3 grid(tiles * tiled_ntiles(a.npb, a.group), p->tgt.n_layers * 2);
+  tiled_kernel<T><<<grid, dim3(256), 0, st>>>(a);
 }
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
@@ -546,7 +635,7 @@ extern "C" kvx_status kvx_translate(const kvx_plan* p, const kvx_io* io_in, void
     const int nb = static_cast<int>(B - b0 < kMaxBatch ? B - b0 : kMaxBatch);
     BatchArgs ba{};
     ba.n = nb;
-    const int rows_per_tile = fused ? kMT : tiled_rows(p->din);
+    const int rows_per_tile = fused ? kMT : kGRows;
     int tiles = 0;
     for (int i = 0; i < nb; ++i) {
       ba.tile_start[i] = tiles;
@@ -611,41 +700,10 @@ extern "C" kvx_status kvx_translate(const kvx_plan* p, const kvx_io* io_in, void
       // allows exactly one)
       const int grid = static_cast<int>(total < p->n_cu ? total : p->n_cu);
       launch_fused(identity, Ds == 128, p->precision, grid, st, a);
+    } else if (p->dtype == KVX_F32) {
+      launch_tiled<float>(p, ss, ts, sk, sv, tk, tv, io, identity, pg, ba, tiles, st);
     } else {
-      const size_t lds = tiled_lds_bytes(p->din);
-      if (p->dtype == KVX_F32) {
-        TiledArgs<float> a{};
-        a.src[0] = reinterpret_cast<const float*>(sk);
-        a.src[1] = reinterpret_cast<const float*>(sv);
-        a.tgt[0] = reinterpret_cast<float*>(tk);
-        a.tgt[1] = reinterpret_cast<float*>(tv);
-        a.w[0] = static_cast<const float*>(p->w[0]);
-        a.w[1] = static_cast<const float*>(p->w[1]);
-        a.ss = ss; a.ts = ts;
-        a.bias[0] = p->bias[0]; a.bias[1] = p->bias[1];
-        a.layer_map = p->layer_map; a.mix = p->mix;
-        a.hs = Hs; a.ds = Ds; a.ht = Ht; a.dt = Dt; a.din = p->din; a.dout = p->dout;
-        a.fs = p->fs; a.ft = p->ft;
-        a.row_ptr = io.row_ptr; a.col_idx = io.col_idx; a.weight = io.weight;
-        a.identity = identity; a.rows = rows_per_tile; a.pg = pg; a.ba = ba;
-        tiled_kernel<float><<<dim3(tiles, Lt, 2), dim3(256), lds, st>>>(a);
-      } else {
-        TiledArgs<bf16_t> a{};
-        a.src[0] = reinterpret_cast<const bf16_t*>(sk);
-        a.src[1] = reinterpret_cast<const bf16_t*>(sv);
-        a.tgt[0] = reinterpret_cast<bf16_t*>(tk);
-        a.tgt[1] = reinterpret_cast<bf16_t*>(tv);
-        a.w[0] = static_cast<const bf16_t*>(p->w[0]);
-        a.w[1] = static_cast<const bf16_t*>(p->w[1]);
-        a.ss = ss; a.ts = ts;
-        a.bias[0] = p->bias[0]; a.bias[1] = p->bias[1];
-        a.layer_map = p->layer_map; a.mix = p->mix;
-        a.hs = Hs; a.ds = Ds; a.ht = Ht; a.dt = Dt; a.din = p->din; a.dout = p->dout;
-        a.fs = p->fs; a.ft = p->ft;
-        a.row_ptr = io.row_ptr; a.col_idx = io.col_idx; a.weight = io.weight;
-        a.identity = identity; a.rows = rows_per_tile; a.pg = pg; a.ba = ba;
-        tiled_kernel<bf16_t><<<dim3(tiles, Lt, 2), dim3(256), lds, st>>>(a);
-      }
+      launch_tiled<bf16_t>(p, ss, ts, sk, sv, tk, tv, io, identity, pg, ba, tiles, st);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return hip_fail(e);
