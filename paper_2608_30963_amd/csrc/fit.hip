@@ -14,8 +14,8 @@
 //                and j >= i over Z and Y (upper Z^T Z blocks and Z^T Y),
 //                v_mfma_f32_32x32x16_bf16 with hi*hi (+ hi*lo + lo*hi);
 // and once per solve:
-//   fit_solve    per system: A = Z^T Z + lam D (fp64), blocked Cholesky,
-//                forward and backward substitution for the Z^T Y columns,
+//   solve_*      per system: A = Z^T Z + lam D (fp64), blocked Cholesky with
+//                the Z^T Y columns carried along, backward substitution,
 //                W = X^T[:din], b = X^T[din].
 #include <hip/hip_runtime.h>
 
@@ -526,9 +526,10 @@ __global__ void __launch_bounds__(256, 2) fit_gram(GramArgs a, int kv) {
 
 struct SolveArgs {
   const float* acc;  // [sys][din_p][F]
-  double* A;         // [group][n][n] workspace, one per system of the launch
-  double* X;         // [group][n][dout] workspace (right-hand sides, then solution)
-  int32_t sys0;      // first system of the launch: system sys0 + blockIdx.y (.x)
+  double* S;         // [group][np + dout][np] workspace: L, below it the right-hand sides'
+                     // rows (Y^T, then X^T)
+  int32_t sys0;      // first system of the launch
+  int32_t ng;        // systems of the launch
   float* w[2];       // [Lt][dout][din]
   float* b[2];       // [Lt][dout] or nullptr
   int32_t* status;   // set to 1 if a pivot is not positive
@@ -539,337 +540,331 @@ struct SolveArgs {
 };
 
 // The solve of each (layer, K|V) system, A = Zt^T Zt + lam D and
-// L L^T X = Zt^T Y in fp64, as a blocked right-looking Cholesky spread over
-// many workgroups: per 32-wide panel, one workgroup per system factors the
-// diagonal block, solves the panel's rows below it and the panel's rows of
-// the forward substitution (L Y = B); then 64 x 64 tiles of the trailing
-// matrix and of the right-hand sides are updated by one workgroup each.  The
-// backward substitution (L^T X = Y) runs panel by panel from the last, again
-// with one workgroup per system for the diagonal block and tiles for the
-// updates of the rows above.
-constexpr int kSB = 32;  // panel width
-constexpr int kST = 64;  // update tile edge
+// L L^T X = Zt^T Y in fp64, as a left-looking blocked Cholesky of the matrix
+// [A; Y^T Zt] -- the right-hand sides are carried as further rows, so their
+// forward substitution is the same operation as the panel rows':
+//   row block r, panel p:  L[r][p] = (A[r][p] - sum_{q<p} L[r][q] L[p][q]^T) L_pp^-T.
+// One launch per 32-wide panel (solve_step); every workgroup forms 32 rows on
+// v_mfma_f64_16x16x4_f64 straight from the accumulators, and the one that owns
+// the next panel's rows also factors its diagonal block and stores the block's
+// inverse in its place (L_pp itself is not needed again).  The backward
+// substitution needs no other workgroup's rows: one launch, 32 right-hand
+// sides per workgroup, which also writes W and b.
+// Bound by the serial chain of the panels (a launch, a product over the
+// earlier panels and a 32 x 32 factorisation each), not by flops: 56 systems
+// of 513 unknowns are 10 Gflop of fp64.  So the eight waves of a workgroup
+// split the contraction four ways (a product then waits for one or two
+// memory latencies instead of up to 16 in a row), and the next diagonal
+// block's sums are formed beside the rows' own, from the same registers.
+// Carrying the right-hand sides in the steps fills the compute units that the
+// shrinking factor leaves idle.  Measured per step 29 us and the backward
+// launch 195 us (56 systems of 513 unknowns, 256 right-hand sides): 0.70 ms a
+// solve, 2.25 ms with four launches per panel for the factor and two for the
+// substitution; 52 systems of 257 unknowns, 1024 right-hand sides: 0.56 ms,
+// 1.5 ms before.  One share of the contraction per workgroup took 51 us a step.
+constexpr int kSB = 32;          // panel width, and rows per workgroup
+constexpr int kSLd = kSB + 2;    // LDS row stride (doubles)
+constexpr int kSK = 4;           // ways a workgroup splits the contraction
+constexpr int kST = 128 * kSK;   // threads: kSK shares x 2 halves of the columns
 
-__device__ __forceinline__ double* sys_A(const SolveArgs& a, int g) {
-  return a.A + static_cast<int64_t>(g) * a.np * a.np;
-}
-__device__ __forceinline__ double* sys_X(const SolveArgs& a, int g) {
-  return a.X + static_cast<int64_t>(g) * a.np * a.dout;
-}
+typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
+typedef __attribute__((__vector_size__(2 * sizeof(double)))) double f64x2;
 
-// Lower triangle of A (ridge on the din weight unknowns, not the bias) and
-// X = Zt^T Y from the upper accumulator blocks.  grid: (chunks, systems).
-__global__ void __launch_bounds__(256) solve_build(SolveArgs a) {
-  const int g = blockIdx.y;
-  const float* acc = a.acc + static_cast<int64_t>(a.sys0 + g) * a.din_p * a.F;
-  double* A = sys_A(a, g);
-  double* X = sys_X(a, g);
-  const int np = a.np;
-  const int64_t nn = static_cast<int64_t>(np) * np;
-  const int64_t total = nn + static_cast<int64_t>(np) * a.dout;
-  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < total;
-       idx += static_cast<int64_t>(gridDim.x) * 256) {
-    if (idx < nn) {
-      const int i = static_cast<int>(idx / np), j = static_cast<int>(idx % np);
-      double v = 0.0;
-      if (i >= a.n || j >= a.n) {
-        v = i == j ? 1.0 : 0.0;
-      } else if (j <= i) {
-        v = acc[static_cast<int64_t>(j) * a.F + i];
-        if (i == j && i < a.din) v += a.lam;
-      }
-      A[idx] = v;
-    } else {
-      const int64_t k = idx - nn;
-      const int i = static_cast<int>(k / a.dout), c = static_cast<int>(k % a.dout);
-      X[k] = i < a.n ? acc[static_cast<int64_t>(i) * a.F + a.din_p + c] : 0.0;
-    }
-  }
+__device__ __forceinline__ double* sys_S(const SolveArgs& a, int g) {
+  return a.S + static_cast<int64_t>(g) * (a.np + a.dout) * a.np;
 }
 
-// Panel kb: factor the diagonal block in LDS and write L_kk back.
-// grid: (systems).
-__global__ void __launch_bounds__(256) solve_panel(SolveArgs a, int kb) {
-  __shared__ double pk[kSB][kSB + 1];
-  const int g = blockIdx.x, tid = threadIdx.x;
-  const int n = a.np;
-  constexpr int kw = kSB;
-  double* A = sys_A(a, g);
-  for (int idx = tid; idx < kSB * kSB; idx += 256) {
-    const int i = idx / kSB, j = idx % kSB;
-    pk[i][j] = (i < kw && j <= i) ? A[static_cast<int64_t>(kb + i) * n + kb + j] : 0.0;
+// Element (r, c), c <= r, of [A; Y^T Zt]: the upper triangle of the
+// accumulators transposed, ridge on the weight unknowns (not the bias).
+__device__ __forceinline__ double sys_elem(const SolveArgs& a, const float* acc, int r, int c) {
+  if (r < a.np) {
+    if (r >= a.n || c >= a.n) return r == c ? 1.0 : 0.0;
+    const double v = acc[static_cast<int64_t>(c) * a.F + r];
+    return r == c && r < a.din ? v + a.lam : v;
   }
-  __syncthreads();
-  bool bad = false;
-  for (int k = 0; k < kw; ++k) {
-    const double dkk = pk[k][k];
-    const bool ok = dkk > 0.0 && isfinite(dkk);
-    bad |= !ok;
-    const double d = ok ? sqrt(dkk) : 1.0;
-    __syncthreads();
-    if (tid == 0) pk[k][k] = d;
-    for (int i = k + 1 + tid; i < kw; i += 256) pk[i][k] /= d;
-    __syncthreads();
-    for (int idx = tid; idx < kSB * kSB; idx += 256) {
-      const int i = idx / kSB, j = idx % kSB;
-      if (i > k && j > k && j <= i && i < kw) pk[i][j] -= pk[i][k] * pk[j][k];
-    }
-    __syncthreads();
-  }
-  if (bad && tid == 0) a.status[0] = 1;
-  for (int idx = tid; idx < kSB * kSB; idx += 256) {
-    const int i = idx / kSB, j = idx % kSB;
-    if (i < kw && j <= i) A[static_cast<int64_t>(kb + i) * n + kb + j] = pk[i][j];
-  }
+  return c < a.n ? acc[static_cast<int64_t>(c) * a.F + a.din_p + (r - a.np)] : 0.0;
 }
 
-// Panel kb, after its factor, `rhs` false: each thread one row below the
-// diagonal block, L[i][kb..] = A[i][kb..] L_kk^-T; `rhs` true: each thread
-// one right-hand side column of the panel's rows of L Y = B (X_k already
-// holds B_k minus the earlier panels' terms).  Separate instantiations, so
-// the compiler does not keep the factor's values live across both.
-// grid: (ceil(items / 256), systems).
-template <bool RHS>
-__global__ void __launch_bounds__(256) solve_panel_rows(SolveArgs a, int kb) {
-  __shared__ double pk[kSB][kSB + 1];
-  const int g = blockIdx.y, tid = threadIdx.x;
-  const int n = a.np, m = a.dout;
-  constexpr int kw = kSB;
-  double* A = sys_A(a, g);
-  double* X = sys_X(a, g);
-  for (int idx = tid; idx < kSB * kSB; idx += 256) {
-    const int i = idx / kSB, j = idx % kSB;
-    pk[i][j] = (i < kw && j <= i) ? A[static_cast<int64_t>(kb + i) * n + kb + j]
-                                  : (i == j ? 1.0 : 0.0);
-  }
-  __syncthreads();
-  const int item = blockIdx.x * 256 + tid;
-  if (item >= (RHS ? m : n - kb - kw)) return;
-  double* base = RHS ? X + static_cast<int64_t>(kb) * m + item
-                     : A + static_cast<int64_t>(kb + kw + item) * n + kb;
-  const int64_t step = RHS ? m : 1;
+// Lane l of v_mfma_f64_16x16x4_f64 holds A[l % 16][l / 16], B[l / 16][l % 16]
+// and D[4 v + l / 16][l % 16] (checked on the device).  The contraction index
+// may be taken in any order that A and B share: a lane reads four consecutive
+// values k + 4 (l / 16) .. +3 of its rows and feeds them to four products.
+__device__ __forceinline__ f64x4 mfma4(const f64x4& x, const f64x4& y, f64x4 c) {
+#pragma unroll
+  for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f64_16x16x4f64(x[e], y[e], c, 0, 0, 0);
+  return c;
+}
+__device__ __forceinline__ f64x4 load4(const double* p) {
+  const f64x2 a = *reinterpret_cast<const f64x2*>(p), b = *reinterpret_cast<const f64x2*>(p + 2);
+  return f64x4{a[0], a[1], b[0], b[1]};
+}
+
+// Lane `lane`'s value in every lane (scalar registers).
+__device__ __forceinline__ double bcast(double x, int lane) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, x);
+  const uint32_t lo = __builtin_amdgcn_readlane(static_cast<uint32_t>(u), lane);
+  const uint32_t hi = __builtin_amdgcn_readlane(static_cast<uint32_t>(u >> 32), lane);
+  return __builtin_bit_cast(double, static_cast<uint64_t>(hi) << 32 | lo);
+}
+
+// Cholesky factor of the 32 x 32 block pk (lower triangle) by one wave; the
+// inverse of the factor goes to out (row stride np, zeros above the diagonal).
+__device__ __forceinline__ void factor_block(const double (*pk)[kSB + 1], double* out, int np,
+                                             int lane, int32_t* status) {
+  // lanes 0..31: the block's rows; lanes 32..63: the identity's, which the
+  // same column operations turn into the rows of L^-T
   double r[kSB];
 #pragma unroll
-  for (int q = 0; q < kSB; ++q) r[q] = q < kw ? base[q * step] : 0.0;
-  // column by column: r_q is final once the earlier columns are subtracted
+  for (int k = 0; k < kSB; ++k) r[k] = lane < kSB ? pk[lane][k] : (k == lane - kSB ? 1.0 : 0.0);
+  bool bad = false;
 #pragma unroll
-  for (int q = 0; q < kSB; ++q) {
-    r[q] /= pk[q][q];
+  for (int k = 0; k < kSB; ++k) {
+    const double d = bcast(r[k], k);
+    const bool ok = d > 0.0 && isfinite(d);
+    bad |= !ok;
+    // 1 / sqrt(d): the hardware estimate and two Newton steps
+    double y = __builtin_amdgcn_rsq(d);
+    y = y * fma(-0.5 * d * y, y, 1.5);
+    y = y * fma(-0.5 * d * y, y, 1.5);
+    r[k] *= ok ? y : 1.0;
 #pragma unroll
-    for (int p = q + 1; p < kSB; ++p) r[p] -= pk[p][q] * r[q];
+    for (int j = k + 1; j < kSB; ++j) r[j] -= r[k] * bcast(r[k], j);
   }
+  if (bad && lane == 0) *status = 1;
+  if (lane >= kSB)
 #pragma unroll
-  for (int q = 0; q < kSB; ++q)
-    if (q < kw) base[q * step] = r[q];
+    for (int k = 0; k < kSB; ++k) out[static_cast<int64_t>(k) * np + lane - kSB] = r[k];
 }
 
-// Trailing update after panel kb: 64 x 64 tiles of the lower triangle of
-// A[t0:, t0:] (A[i][j] -= sum_q L[i][kb+q] L[j][kb+q]) and of X[t0:, :]
-// (X[i][c] -= sum_q L[i][kb+q] Y[kb+q][c]), t0 = kb + 32.  Thread: a 4 x 4
-// block of the tile.  grid: (tiles, systems).
-__global__ void __launch_bounds__(256) solve_update(SolveArgs a, int kb) {
-  __shared__ double P[kST][kSB + 1];  // L rows of the tile's rows
-  __shared__ double Q[kST][kSB + 1];  // L rows of the tile's columns, or Y_k transposed
-  const int g = blockIdx.y, tid = threadIdx.x;
-  const int n = a.np, m = a.dout;
-  constexpr int kw = kSB;
-  const int t0 = kb + kw;
-  const int nt = (n - t0 + kST - 1) / kST;
-  const int ntri = nt * (nt + 1) / 2;
-  const int nct = (m + kST - 1) / kST;
-  int tile = blockIdx.x;
-  if (tile >= ntri + nt * nct) return;
-  double* A = sys_A(a, g);
-  double* X = sys_X(a, g);
-  const bool onA = tile < ntri;
-  int ti, tj;
-  if (onA) {
-    ti = 0;
-    while ((ti + 1) * (ti + 2) / 2 <= tile) ++ti;
-    tj = tile - ti * (ti + 1) / 2;
-  } else {
-    tile -= ntri;
-    ti = tile / nct;
-    tj = tile % nct;
-  }
-  const int i0 = t0 + ti * kST;
-  const int j0 = onA ? t0 + tj * kST : tj * kST;
-  for (int idx = tid; idx < kST * kSB; idx += 256) {
-    const int r = idx / kSB, q = idx % kSB;
-    P[r][q] = (i0 + r < n && q < kw) ? A[static_cast<int64_t>(i0 + r) * n + kb + q] : 0.0;
-    if (onA)
-      Q[r][q] = (j0 + r < n && q < kw) ? A[static_cast<int64_t>(j0 + r) * n + kb + q] : 0.0;
-    else  // Q[c][q] = Y[kb + q][j0 + c]
-      Q[r][q] = (j0 + r < m && q < kw) ? X[static_cast<int64_t>(kb + q) * m + j0 + r] : 0.0;
+// Panel 0's diagonal block.  grid: (systems).
+__global__ void __launch_bounds__(kST) solve_first(SolveArgs a) {
+  __shared__ double pk[kSB][kSB + 1];
+  const int g = blockIdx.x;
+  const float* acc = a.acc + static_cast<int64_t>(a.sys0 + g) * a.din_p * a.F;
+  for (int idx = threadIdx.x; idx < kSB * kSB; idx += kST) {
+    const int i = idx / kSB, j = idx % kSB;
+    pk[i][j] = i >= j ? sys_elem(a, acc, i, j) : 0.0;
   }
   __syncthreads();
-  const int rb = (tid / 16) * 4, cb = (tid % 16) * 4;
-  double s[4][4];
+  if (threadIdx.x < 64) factor_block(pk, sys_S(a, g), a.np, threadIdx.x, a.status);
+}
+
+// Panel p of 32 rows below it (matrix rows, then right-hand sides) and, where
+// these are the next panel's, its diagonal block.  grid: (row blocks * systems).
+__global__ void __launch_bounds__(kST, 4) solve_step(SolveArgs a, int p) {
+  __shared__ double red[kSK][kSB][kSB + 1];  // the shares' sums
+  __shared__ __attribute__((aligned(16))) double cl[kSB][kSLd];
+  __shared__ double pk[kSB][kSB + 1];
+  // systems fastest: the workgroups with a diagonal block to factor, the
+  // longest, start first, and a system's workgroups stay on one or two XCDs
+  // (workgroups are dealt to the eight XCDs in turn)
+  const int g = blockIdx.x % a.ng, blk = blockIdx.x / a.ng;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int np = a.np, rows = np + a.dout;
+  const int c0 = kSB * p, r0 = c0 + kSB * (1 + blk);
+  const bool next = blk == 0 && r0 < np;  // rows of the next panel
+  const float* acc = a.acc + static_cast<int64_t>(a.sys0 + g) * a.din_p * a.F;
+  double* S = sys_S(a, g);
+  const int l16 = lane % 16, g4 = 4 * (lane / 16);
+  // this thread's two elements of A[rows][p] (row fastest: coalesced), and of
+  // the next diagonal block
+  double av[2], dv[2];
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+  for (int e = 0; e < 2; ++e) {
+    const int idx = tid + kST * e, c = idx / kSB, r = idx % kSB;
+    av[e] = r0 + r < rows ? sys_elem(a, acc, r0 + r, c0 + c) : 0.0;
+    dv[e] = next && r >= c ? sys_elem(a, acc, r0 + r, r0 + c) : 0.0;
+  }
+  // the inverse of L_pp, for the waves that apply it
+  const int ti = (w % 4) / 2, tj = w % 2;
+  f64x4 li[2];
 #pragma unroll
-    for (int y = 0; y < 4; ++y) s[x][y] = 0.0;
-#pragma unroll 4
-  for (int q = 0; q < kw; ++q) {
-    double pv[4], qv[4];
+  for (int u = 0; u < 2; ++u)
+    li[u] = load4(S + static_cast<int64_t>(c0 + 16 * tj + l16) * np + c0 + 16 * u + g4);
+  // wave: share w / 2 of the panels, columns 16 (w % 2) .. +15
+  const int share = w / 2, half = w % 2;
+  const double* pa0 = S + static_cast<int64_t>(min(r0 + l16, rows - 1)) * np + g4;
+  const double* pa1 = S + static_cast<int64_t>(min(r0 + 16 + l16, rows - 1)) * np + g4;
+  const double* pb = S + static_cast<int64_t>(c0 + 16 * half + l16) * np + g4;
+  f64x4 s[2] = {}, d[2] = {};
+  for (int q = share; q < p; q += kSK) {
+    const int k = kSB * q;
+    f64x4 x0[2], x1[2], y[2];
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      pv[x] = P[rb + x][q];
-      qv[x] = Q[cb + x][q];
+    for (int u = 0; u < 2; ++u) {
+      x0[u] = load4(pa0 + k + 16 * u);
+      x1[u] = load4(pa1 + k + 16 * u);
+      y[u] = load4(pb + k + 16 * u);
     }
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) s[x][y] += pv[x] * qv[y];
-  }
-#pragma unroll
-  for (int x = 0; x < 4; ++x)
-#pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int i = i0 + rb + x, j = j0 + cb + y;
-      if (onA) {
-        if (i < n && j <= i) A[static_cast<int64_t>(i) * n + j] -= s[x][y];
-      } else if (i < n && j < m) {
-        X[static_cast<int64_t>(i) * m + j] -= s[x][y];
+    for (int u = 0; u < 2; ++u) {
+      s[0] = mfma4(x0[u], y[u], s[0]);
+      s[1] = mfma4(x1[u], y[u], s[1]);
+      if (next) {
+        const f64x4 z = half ? x1[u] : x0[u];
+        d[0] = mfma4(x0[u], z, d[0]);
+        d[1] = mfma4(x1[u], z, d[1]);
       }
     }
-}
-
-// Backward substitution, panel kb (from the last): L_kk^T X_k = X_k, one
-// right-hand side column per thread.  grid: (ceil(dout / 256), systems).
-__global__ void __launch_bounds__(256) solve_back_diag(SolveArgs a, int kb) {
-  __shared__ double pk[kSB][kSB + 1];
-  const int g = blockIdx.y, tid = threadIdx.x;
-  const int n = a.np, m = a.dout;
-  constexpr int kw = kSB;
-  const double* A = sys_A(a, g);
-  double* X = sys_X(a, g);
-  for (int idx = tid; idx < kSB * kSB; idx += 256) {
-    const int i = idx / kSB, j = idx % kSB;
-    pk[i][j] = (i < kw && j <= i) ? A[static_cast<int64_t>(kb + i) * n + kb + j]
-                                  : (i == j ? 1.0 : 0.0);
+  }
+  auto put = [&](const f64x4(&v)[2]) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) red[share][16 * t + 4 * e + lane / 16][16 * half + l16] = v[t][e];
+  };
+  auto total = [&](int i, int j) __attribute__((always_inline)) {
+    double v = 0.0;
+#pragma unroll
+    for (int k = 0; k < kSK; ++k) v += red[k][i][j];
+    return v;
+  };
+  put(s);
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 2; ++e) {
+    const int idx = tid + kST * e, c = idx / kSB, r = idx % kSB;
+    cl[r][c] = av[e] - total(r, c);
   }
   __syncthreads();
-  const int c = blockIdx.x * 256 + tid;
-  if (c >= m) return;
-  double x[kSB];
+  f64x4 x = {};
+  if (w < 4) {
 #pragma unroll
-  for (int q = 0; q < kSB; ++q) x[q] = q < kw ? X[static_cast<int64_t>(kb + q) * m + c] : 0.0;
+    for (int u = 0; u < 2; ++u) x = mfma4(load4(&cl[16 * ti + l16][16 * u + g4]), li[u], x);
 #pragma unroll
-  for (int q = kSB - 1; q >= 0; --q) {
-    double v = x[q];
-#pragma unroll
-    for (int p = q + 1; p < kSB; ++p) v -= pk[p][q] * x[p];
-    x[q] = v / pk[q][q];
+    for (int v = 0; v < 4; ++v) {
+      const int r = r0 + 16 * ti + 4 * v + lane / 16;
+      if (r < rows) S[static_cast<int64_t>(r) * np + c0 + 16 * tj + l16] = x[v];
+    }
   }
-#pragma unroll
-  for (int q = 0; q < kSB; ++q)
-    if (q < kw) X[static_cast<int64_t>(kb + q) * m + c] = x[q];
-}
-
-// Backward update after panel kb: rows above it, X[j][c] -= sum_q
-// L[kb+q][j] X[kb+q][c] for j < kb, in 64 x 64 tiles.  grid: (tiles, systems).
-__global__ void __launch_bounds__(256) solve_back_update(SolveArgs a, int kb) {
-  __shared__ double P[kST][kSB + 1];  // P[r][q] = L[kb + q][j0 + r]
-  __shared__ double Q[kST][kSB + 1];  // Q[c][q] = X[kb + q][c0 + c]
-  const int g = blockIdx.y, tid = threadIdx.x;
-  const int n = a.np, m = a.dout;
-  constexpr int kw = kSB;
-  const int nct = (m + kST - 1) / kST;
-  const int nrt = (kb + kST - 1) / kST;
-  if (static_cast<int>(blockIdx.x) >= nrt * nct) return;
-  const double* A = sys_A(a, g);
-  double* X = sys_X(a, g);
-  const int j0 = (blockIdx.x / nct) * kST, c0 = (blockIdx.x % nct) * kST;
-  for (int idx = tid; idx < kST * kSB; idx += 256) {
-    const int q = idx / kST, r = idx % kST;
-    P[r][q] = (q < kw && j0 + r < kb) ? A[static_cast<int64_t>(kb + q) * n + j0 + r] : 0.0;
-    Q[r][q] = (q < kw && c0 + r < m) ? X[static_cast<int64_t>(kb + q) * m + c0 + r] : 0.0;
-  }
+  if (!next) return;  // uniform
+  // the next diagonal block: its sums over the earlier panels, and over this
+  // one from the rows just formed
   __syncthreads();
-  const int rb = (tid / 16) * 4, cb = (tid % 16) * 4;
-  double s[4][4];
+  put(d);
+  if (w < 4)
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+    for (int v = 0; v < 4; ++v) cl[16 * ti + 4 * v + lane / 16][16 * tj + l16] = x[v];
+  __syncthreads();
 #pragma unroll
-    for (int y = 0; y < 4; ++y) s[x][y] = 0.0;
-#pragma unroll 4
-  for (int q = 0; q < kw; ++q) {
-    double pv[4], qv[4];
-#pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      pv[x] = P[rb + x][q];
-      qv[x] = Q[cb + x][q];
-    }
-#pragma unroll
-    for (int x = 0; x < 4; ++x)
-#pragma unroll
-      for (int y = 0; y < 4; ++y) s[x][y] += pv[x] * qv[y];
+  for (int e = 0; e < 2; ++e) {
+    const int idx = tid + kST * e, c = idx / kSB, r = idx % kSB;
+    pk[r][c] = dv[e] - total(r, c);
   }
+  f64x4 y = {};
+  if (w < 4)
 #pragma unroll
-  for (int x = 0; x < 4; ++x)
+    for (int u = 0; u < 2; ++u)
+      y = mfma4(load4(&cl[16 * ti + l16][16 * u + g4]), load4(&cl[16 * tj + l16][16 * u + g4]), y);
+  __syncthreads();
+  if (w < 4)
 #pragma unroll
-    for (int y = 0; y < 4; ++y) {
-      const int j = j0 + rb + x, c = c0 + cb + y;
-      if (j < kb && c < m) X[static_cast<int64_t>(j) * m + c] -= s[x][y];
-    }
+    for (int v = 0; v < 4; ++v) pk[16 * ti + 4 * v + lane / 16][16 * tj + l16] -= y[v];
+  __syncthreads();
+  if (w == 0) factor_block(pk, S + static_cast<int64_t>(r0) * np + r0, np, lane, a.status);
 }
 
-// W = X[:din]^T (nn.Linear order) and b = X[din].  grid: (chunks, systems).
-__global__ void __launch_bounds__(256) solve_write(SolveArgs a) {
-  const int g = blockIdx.y;
-  const int sys = a.sys0 + g;
-  const int l = sys / 2, kv = sys % 2, m = a.dout;
-  const double* X = sys_X(a, g);
-  float* w = a.w[kv] + static_cast<int64_t>(l) * m * a.din;
-  const int64_t total = static_cast<int64_t>(m) * a.din;
-  for (int64_t idx = blockIdx.x * 256 + threadIdx.x; idx < total;
-       idx += static_cast<int64_t>(gridDim.x) * 256) {
-    const int c = static_cast<int>(idx / a.din), i = static_cast<int>(idx % a.din);
-    w[idx] = static_cast<float>(X[static_cast<int64_t>(i) * m + c]);
+// Backward substitution X^T[c][p] = (Y^T[c][p] - sum_{q>p} X^T[c][q] L[q][p]) L_pp^-1
+// of 32 right-hand sides, panel by panel from the last, and their rows of W
+// (nn.Linear order) and b.  grid: (ceil(dout / 32) * systems).
+__global__ void __launch_bounds__(kST, 4) solve_back(SolveArgs a) {
+  __shared__ double red[kSK][kSB][kSB + 1];
+  __shared__ __attribute__((aligned(16))) double cl[kSB][kSLd];
+  const int g = blockIdx.x % a.ng, blk = blockIdx.x / a.ng;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int np = a.np, m = a.dout;
+  const int l16 = lane % 16, g4 = 4 * (lane / 16);
+  const int sys = a.sys0 + g, l = sys / 2, kv = sys % 2;
+  double* S = sys_S(a, g);
+  double* X = S + static_cast<int64_t>(np) * np;
+  float* wo = a.w[kv] + static_cast<int64_t>(l) * m * a.din;
+  float* bo = a.b[kv] ? a.b[kv] + static_cast<int64_t>(l) * m : nullptr;
+  const int r0 = kSB * blk;  // first right-hand side
+  const int ti = (w % 4) / 2, tj = w % 2, share = w / 2, half = w % 2;
+  const double* pa0 = X + static_cast<int64_t>(min(r0 + l16, m - 1)) * np + g4;
+  const double* pa1 = X + static_cast<int64_t>(min(r0 + 16 + l16, m - 1)) * np + g4;
+  const int64_t n1 = np;
+  for (int p = np / kSB - 1; p >= 0; --p) {
+    const int c0 = kSB * p;
+    // lane: column c of rows k + 4 (lane / 16) .. +3
+    auto cols = [&](int k, int c) __attribute__((always_inline)) {
+      const double* q = S + (k + g4) * n1 + c + l16;
+      return f64x4{q[0], q[n1], q[2 * n1], q[3 * n1]};
+    };
+    f64x4 li[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) li[u] = cols(c0 + 16 * u, c0 + 16 * tj);
+    double yv[2];  // Y of this thread's elements
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int idx = tid + kST * e, r = idx / kSB, c = idx % kSB;
+      yv[e] = X[min(r0 + r, m - 1) * n1 + c0 + c];
+    }
+    f64x4 s[2] = {};
+    for (int q = p + 1 + share; q < np / kSB; q += kSK) {
+      const int k = kSB * q;
+      f64x4 x0[2], x1[2], y[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        x0[u] = load4(pa0 + k + 16 * u);
+        x1[u] = load4(pa1 + k + 16 * u);
+        y[u] = cols(k + 16 * u, c0 + 16 * half);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        s[0] = mfma4(x0[u], y[u], s[0]);
+        s[1] = mfma4(x1[u], y[u], s[1]);
+      }
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        red[share][16 * t + 4 * e + lane / 16][16 * half + l16] = s[t][e];
+    __syncthreads();
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      const int idx = tid + kST * e, r = idx / kSB, c = idx % kSB;
+      double v = 0.0;
+#pragma unroll
+      for (int k = 0; k < kSK; ++k) v += red[k][r][c];
+      cl[r][c] = yv[e] - v;
+    }
+    __syncthreads();
+    if (w < 4) {
+      f64x4 x = {};
+#pragma unroll
+      for (int u = 0; u < 2; ++u) x = mfma4(load4(&cl[16 * ti + l16][16 * u + g4]), li[u], x);
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int c = r0 + 16 * ti + 4 * v + lane / 16, i = c0 + 16 * tj + l16;
+        if (c >= m) continue;
+        X[c * n1 + i] = x[v];
+        if (i < a.din)
+          wo[static_cast<int64_t>(c) * a.din + i] = static_cast<float>(x[v]);
+        else if (i == a.din && a.fit_bias && bo)
+          bo[c] = static_cast<float>(x[v]);
+      }
+    }
+    __syncthreads();  // X[.][p] is written before the next panel reads it
   }
-  if (a.b[kv] && blockIdx.x == 0)
-    for (int c = threadIdx.x; c < m; c += 256)
-      a.b[kv][static_cast<int64_t>(l) * m + c] =
-          a.fit_bias ? static_cast<float>(X[static_cast<int64_t>(a.din) * m + c]) : 0.f;
+  if (bo && !a.fit_bias && tid < kSB && r0 + tid < m) bo[r0 + tid] = 0.f;
 }
 
 // Enqueue the solve of `ng` systems (sa.sys0 ..) whose workspaces start at
-// sa.A and sa.X.
-kvx_status enqueue_solve(const SolveArgs& sa, int ng, hipStream_t st) {
-  const int n = sa.np, m = sa.dout;
-  const unsigned chunks = static_cast<unsigned>(
-      std::min<int64_t>(1024, (int64_t(n) * (n + m) + 2047) / 2048));
-  solve_build<<<dim3(chunks, ng), dim3(256), 0, st>>>(sa);
+// sa.S.
+kvx_status enqueue_solve(SolveArgs sa, int ng, hipStream_t st) {
+  sa.ng = ng;
+  solve_first<<<dim3(ng), dim3(kST), 0, st>>>(sa);
   FIT_HIP(hipGetLastError());
-  const int nct = (m + kST - 1) / kST;
-  for (int kb = 0; kb < n; kb += kSB) {
-    solve_panel<<<dim3(ng), dim3(256), 0, st>>>(sa, kb);
+  for (int p = 0; p < sa.np / kSB; ++p) {
+    const int rows = sa.np + sa.dout - kSB * (p + 1);
+    solve_step<<<dim3((rows + kSB - 1) / kSB * ng), dim3(kST), 0, st>>>(sa, p);
     FIT_HIP(hipGetLastError());
-    const int t0 = kb + std::min(kSB, n - kb);
-    if (t0 < n) {
-      solve_panel_rows<false><<<dim3((n - t0 + 255) / 256, ng), dim3(256), 0, st>>>(sa, kb);
-      FIT_HIP(hipGetLastError());
-    }
-    solve_panel_rows<true><<<dim3((m + 255) / 256, ng), dim3(256), 0, st>>>(sa, kb);
-    FIT_HIP(hipGetLastError());
-    if (t0 < n) {
-      const int nt = (n - t0 + kST - 1) / kST;
-      solve_update<<<dim3(nt * (nt + 1) / 2 + nt * nct, ng), dim3(256), 0, st>>>(sa, kb);
-      FIT_HIP(hipGetLastError());
-    }
   }
-  for (int kb = (n - 1) / kSB * kSB; kb >= 0; kb -= kSB) {
-    solve_back_diag<<<dim3((m + 255) / 256, ng), dim3(256), 0, st>>>(sa, kb);
-    FIT_HIP(hipGetLastError());
-    if (kb > 0) {
-      solve_back_update<<<dim3(((kb + kST - 1) / kST) * nct, ng), dim3(256), 0, st>>>(sa, kb);
-      FIT_HIP(hipGetLastError());
-    }
-  }
-  const unsigned wchunks = static_cast<unsigned>(
-      std::min<int64_t>(256, (int64_t(m) * sa.din + 2047) / 2048));
-  solve_write<<<dim3(std::max(1u, wchunks), ng), dim3(256), 0, st>>>(sa);
+  solve_back<<<dim3((sa.dout + kSB - 1) / kSB * ng), dim3(kST), 0, st>>>(sa);
   FIT_HIP(hipGetLastError());
   return KVX_OK;
 }
@@ -1238,8 +1233,7 @@ kvx_status kvx_fit_solve(kvx_fit* f, double lambda, float* w_k, float* w_v, floa
   FIT_HIP(hipGetLastError());
   SolveArgs sa{};
   sa.acc = f->acc;
-  sa.A = reinterpret_cast<double*>(base);
-  sa.X = reinterpret_cast<double*>(base + abytes);
+  sa.S = reinterpret_cast<double*>(base);
   sa.sys0 = 0;
   sa.w[0] = w_k;
   sa.w[1] = w_v;
@@ -1285,8 +1279,7 @@ kvx_status kvx_fit_solve_noalloc(kvx_fit* f, double lambda, float* w_k, float* w
   FIT_HIP(hipGetLastError());
   SolveArgs sa{};
   sa.acc = f->acc;
-  sa.A = reinterpret_cast<double*>(base);
-  sa.X = reinterpret_cast<double*>(base + size_t(g) * np * np * sizeof(double));
+  sa.S = reinterpret_cast<double*>(base);
   sa.w[0] = w_k;
   sa.w[1] = w_v;
   sa.b[0] = b_k;

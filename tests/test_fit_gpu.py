@@ -271,3 +271,19 @@ def test_fit_full_size_qwen_4k_all_layers():
             worst_rel, worst_obj = max(worst_rel, rel), max(worst_obj, jo / jr - 1)
         print(f"[fit] full size {'KV'[which]}: worst W rel err {worst_rel:.2e}, "
               f"worst objective excess {worst_obj:.2e}", flush=True)
+
+
+@pytest.mark.parametrize("din,dout,bias", [
+    (16, 16, False), (16, 48, True), (32, 16, False), (32, 32, True), (64, 80, False),
+    (64, 64, True), (160, 16, True), (288, 96, False)],
+    ids=lambda x: str(x))
+def test_fit_solve_panel_edges(din, dout, bias):
+    """The solve at the edges of its 32-wide panels: one unknown past a panel
+    (the bias), whole panels, a half panel, fewer right-hand sides than a
+    block, and more panels than the contraction's shares."""
+    spec = _spec(src=S.ModelShape(2, din // 16, 16, 1.0e4), tgt=S.ModelShape(2, dout // 16, 16, 1.0e6),
+                 src_tokens=400, batch=2, bias_std=0.3 if bias else 0.0)
+    prob = S.make_problem(spec)
+    tk, tv = _native(prob, noise=0.05)
+    got, _ = _gpu_fit(prob, tk, tv, lam=1.0, fit_bias=bias)
+    _compare(prob, tk, tv, got, 1.0, bias, 1e-3, f"{din}x{dout}")
