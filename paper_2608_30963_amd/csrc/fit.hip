@@ -940,6 +940,7 @@ struct kvx_fit {
   float* acc = nullptr;        // [Lt * 2][din_p][F]
   void* prep = nullptr;        // prepared operands X^T
   size_t prep_bytes = 0;
+  int prep_shift = 32;         // log2 of the most bytes to use (30 once 2^32 did not fit)
   void* solve_buf = nullptr;
   size_t solve_bytes = 0;
   int64_t rows = 0;
@@ -1090,19 +1091,34 @@ kvx_status kvx_fit_accumulate(kvx_fit* f, const kvx_fit_io* io_in, void* stream)
     ctx.row0[nb] = r;
     if (r == 0) continue;
     const int32_t rp = static_cast<int32_t>(round_up(r, kPrepRows));
-    // layer groups sized so the prepared operands fit in 1 GiB
+    // Layer groups sized so that the prepared operands fit the scratch.  A
+    // group's Gram launch has 18 workgroups per system at din 512 and takes
+    // two per compute unit, so small groups leave it mostly idle: 16384 rows
+    // of 28 layers [512 -> 256] took 1.95 ms in three groups (1 GiB), 1.04 ms
+    // in one (2.8 GB).  A device without room for the larger scratch gets the
+    // smaller groups.
     const size_t per_layer = size_t(2) * 2 * f->F2 * rp * sizeof(bf16_t);
-    const int64_t lg = std::max<int64_t>(1, std::min<int64_t>(Lt, (size_t(1) << 30) / per_layer));
-    const size_t need = per_layer * lg;
-    if (need > f->prep_bytes) {
+    auto group = [&](int shift) {
+      return std::max<int64_t>(1, std::min<int64_t>(Lt, (size_t(1) << shift) / per_layer));
+    };
+    int64_t lg = group(f->prep_shift);
+    if (per_layer * lg > f->prep_bytes) {
       if (f->prep) {
         FIT_HIP(hipStreamSynchronize(st));
         FIT_HIP(hipFree(f->prep));
         f->prep = nullptr;
         f->prep_bytes = 0;
       }
-      FIT_HIP(hipMalloc(&f->prep, need));
-      f->prep_bytes = need;
+      hipError_t e = hipMalloc(&f->prep, per_layer * lg);
+      if (e == hipErrorOutOfMemory && group(30) < lg) {
+        (void)hipGetLastError();  // handled: not the next launch's error
+        f->prep_shift = 30;
+        lg = group(30);
+        e = hipMalloc(&f->prep, per_layer * lg);
+      }
+      if (e != hipSuccess) f->prep = nullptr;
+      FIT_HIP(e);
+      f->prep_bytes = per_layer * lg;
     }
     const Strides ss{io.src_stride[0], io.src_stride[1], io.src_stride[2], io.src_stride[3]};
     const Strides ts{io.tgt_stride[0], io.tgt_stride[1], io.tgt_stride[2], io.tgt_stride[3]};
