@@ -447,7 +447,11 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
   __shared__ double fsl[kMaxHalfDim];
   // span maps: cos / sin of the source rotation by d = -kDTab .. kDTab
   // positions, [d + kDTab][i] for i < kTabHalf (source head_dim <= 128)
-  __shared__ float2 rotd[(2 * kDTab + 1) * kTabHalf];
+  __shared__ __attribute__((aligned(16))) float2 rotd[(2 * kDTab + 1) * kTabHalf];
+  // resident order: alignment entries of the row tile's rows, {first entry,
+  // entries, token and weight of the first}, {tokens and weights of the
+  // second and third}
+  __shared__ int4 rinf[RES ? kMT : 1][2];
   // target RoPE: theta_i / 2pi, and cos/sin of the rotation by 32 positions
   __shared__ double ftl[kMaxHalfDim];
   __shared__ float2 rot32[kMaxHalfDim];
@@ -568,8 +572,7 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
     const int j0 = hp0 / a.hs, h0 = hp0 % a.hs, i00 = (8 * g) % half;
     // Position of a chunk: its tile, chunk index in the tile, this thread's
     // group; advanced one chunk at a time (no divisions in the step loop).
-    // ord: tile ordinal within this workgroup's range (resident order: of the
-    // first tile of the chunk's row-tile group in the range)
+    // ord: tile ordinal within this workgroup's range
     struct ChunkPos {
       Tile T;
       int c, j, h, i0, ord;
@@ -577,16 +580,8 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
     auto advance_pos = [&](ChunkPos& P) KVX_INLINE {
       if (++P.c == nch) {
         P.c = 0;
-        if constexpr (RES) {
-          // the next (layer, row tile, K|V) group: skip this group's other N tiles
-          const int k = n_tiles - P.T.nt;
-          P.ord += k;
-          if (P.ord < ntw)
-            for (int i = 0; i < k; ++i) next_tile(P.T);
-        } else {
-          ++P.ord;
-          if (P.ord < ntw) next_tile(P.T);
-        }
+        ++P.ord;
+        if (P.ord < ntw) next_tile(P.T);
         P.j = j0;
         P.h = h0;
         P.i0 = i00;
@@ -605,9 +600,6 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
       const int ls = lmap[P.T.l * a.mix + P.j];
       return a.src[P.T.kv] + ls * a.ss.l + P.T.b * a.ss.b + P.h * a.ss.h + P.i0;
     };
-    // chunks this workgroup's producers transform: one per chunk step, or, in
-    // the resident order, nch per row-tile group its range touches
-    const int nprod = RES ? (tile_at(tfirst).nt + ntw + n_tiles - 1) / n_tiles * nch : nchunks;
     ChunkPos fpos;
     fpos.T = tile_at(tfirst);
     fpos.c = 0;
@@ -854,17 +846,17 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
 
     // chunk cs is consumed at step (its tile ordinal) * spt + (its index in the
     // tile) and written into that step's buffer during the step before.
-    fetch_issue(fetch_addr(true), rA, true);
-    fetch_issue(fetch_addr(nprod > 1), rB, nprod > 1);
-    if constexpr (kDepth == 3) fetch_issue(fetch_addr(nprod > 2), rC, nprod > 2);
-    {
-      const bf16_t* gp = fetch_addr(nprod > kDepth);
+    if constexpr (!RES) {
+      fetch_issue(fetch_addr(true), rA, true);
+      fetch_issue(fetch_addr(nchunks > 1), rB, nchunks > 1);
+      if constexpr (kDepth == 3) fetch_issue(fetch_addr(nchunks > 2), rC, nchunks > 2);
+      const bf16_t* gp = fetch_addr(nchunks > kDepth);
       second_issue(rA, true);
       transform(rA, lds, lds + kPlane);
-      second_issue(rB, nprod > 1);
-      fetch_issue(gp, rA, nprod > kDepth);
+      second_issue(rB, nchunks > 1);
+      fetch_issue(gp, rA, nchunks > kDepth);
+      lds_barrier();
     }
-    lds_barrier();
     // Step s ends with a barrier; in an epilogue step (sc == nch) the
     // consumers stage the finished tile in buffer s % 2 and the producers
     // write its rows (the consumers issue no global stores, so their weight
@@ -923,45 +915,302 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
       if constexpr (!kDirect)
         if (sc == 0) store_tile((s - 1) & 1);
     };
-    // Step in which the chunk at P is written: the step before its first use
-    // (step ord * spt + c, buffer s % 2) -- or, in the resident order, where
-    // chunk c of a group lives in buffer c, the step after the previous
-    // group's last use of buffer c.
-    auto write_step = [&](const ChunkPos& P) KVX_INLINE -> int {
-      if constexpr (RES)
-        return P.ord == 0 ? P.c - 1 : (P.ord - 1) * spt + P.c + 1;
-      else
-        return P.ord * spt + P.c - 1;
-    };
+    if constexpr (RES) {
+      // Resident order.  The chunks of a row-tile group (layer, row tile,
+      // K|V) serve all of its N tiles, so a group has spt * n_tiles steps and
+      // only nch of them hand over chunks: chunk c may be written from the
+      // step after its buffer's last use by the previous group.  The
+      // producers therefore transform the next group's chunks in registers,
+      // spread evenly over the steps before that, and the hand-over steps
+      // only move finished operands to LDS.  A unit's raw pieces (the first
+      // two entries) and its operands (two planes) are 64 bytes each, so the
+      // transform is in place: 128 registers hold both chunks, and the rows'
+      // entries stay in LDS.  Before, the transform ran within the two
+      // hand-over steps, which took 17-21 k cycles against 6-10 k for the
+      // others: 26 layers [256 -> 1024], spans of 1-3, 4096 tokens 0.189 ->
+      // 0.171 ms, 8 x 8192 tokens 2.55 -> 2.45 ms; skipping the transform
+      // altogether would give another 3.5%.
+      const bool two = nch > 1;
+      int jc[2], hc[2], ic[2];  // this thread's 8-pair group of each chunk
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int hp = (64 * c + 8 * g) / half;
+        jc[c] = hp / a.hs;
+        hc[c] = hp % a.hs;
+        ic[c] = (64 * c + 8 * g) % half;
+      }
+      auto chunk_ptr = [&](const Tile& T, int c) KVX_INLINE -> const bf16_t* {
+        return a.src[T.kv] + lmap[T.l * a.mix + jc[c]] * a.ss.l + T.b * a.ss.b + hc[c] * a.ss.h +
+               ic[c];
+      };
+      // Entries of T's rows.  A wave fills the 32 rows that its own threads
+      // transform, so no barrier is needed.  Unconditional loads: a row past
+      // the context's end reads the last row's pointers and has no entries,
+      // an absent entry reads the zero sink (weight 0) and keeps the first
+      // one's token.
+      auto load_rows = [&](const Tile& T) KVX_INLINE {
+        const int ln = tid % 32;
+        const int r = tid / 64 * 8 + ln % 8 + 32 * (ln / 8);
+        const int t = T.t0 + r;
+        const int tc = t < T.tt ? t : T.tt - 1;
+        const int e0 = a.row_ptr[T.rb + tc];
+        const int n = t < T.tt ? a.row_ptr[T.rb + tc + 1] - e0 : 0;
+        const int32_t* zi = reinterpret_cast<const int32_t*>(a.zsink);
+        int k[3], w[3];
+#pragma unroll
+        for (int e = 0; e < 3; ++e) {
+          k[e] = *(n > e ? a.col_idx + e0 + e : zi);
+          w[e] = *(n > e ? reinterpret_cast<const int32_t*>(a.weight) + e0 + e : zi);
+          if (e > 0) k[e] = n > e ? k[e] : k[0];
+        }
+        if (tid % 64 < 32) {
+          rinf[r][0] = make_int4(e0, n, k[0], w[0]);
+          rinf[r][1] = make_int4(k[1], w[1], k[2], w[2]);
+        }
+      };
+      // first and second entries of every unit of chunk c
+      auto issue = [&](const Tile& T, int c, uint4 (&x)[kUnits][4]) KVX_INLINE {
+        const bf16_t* gp = chunk_ptr(T, c);
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+          const int4 r0 = rinf[tid / 8 + 32 * u][0], r1 = rinf[tid / 8 + 32 * u][1];
+          const bf16_t* p = r0.y > 0 ? gp + r0.z * a.ss.t : a.zsink;
+          const bf16_t* q = r0.y > 1 ? gp + r1.x * a.ss.t : a.zsink;
+          x[u][0] = ld_src<STREAM>(p);
+          x[u][1] = ld_src<STREAM>(p + half);
+          x[u][2] = ld_src<STREAM>(q);
+          x[u][3] = ld_src<STREAM>(q + half);
+        }
+      };
+      uint4 y[2];  // third entry of the unit that is transformed next
+      auto issue3 = [&](const bf16_t* gp, int u) KVX_INLINE {
+        const int n = rinf[tid / 8 + 32 * u][0].y;
+        const int k2 = rinf[tid / 8 + 32 * u][1].z;
+        const bf16_t* p = n > 2 ? gp + k2 * a.ss.t : a.zsink;
+        y[0] = ld_src<STREAM>(p);
+        y[1] = ld_src<STREAM>(p + half);
+      };
+      // De-rotate (K) and pool one unit.  K is pooled in the first entry's
+      // frame, R(-k0) (w0 x0 + sum_e w_e R(-(k_e - k0)) x_e): one angle per
+      // row and frequency, the relative rotations of nearby tokens from rotd
+      // (when all rows of the wave are that near: one path for the wave).
+      auto unit = [&](uint4 (&x)[4], const bf16_t* gp, int u, int i0, bool is_k) KVX_INLINE {
+        const int4 r0 = rinf[tid / 8 + 32 * u][0], r1 = rinf[tid / 8 + 32 * u][1];
+        const int n = r0.y, k0 = r0.z;
+        const float w0 = __int_as_float(r0.w), w1 = __int_as_float(r1.y);
+        const float w2 = __int_as_float(r1.w);
+        const bool any3 = __any(n > 2);
+        float x0[8], x1[8], v0[8], v1[8], z0[8], z1[8];
+        unpack8(x[0], x0);
+        unpack8(x[1], x1);
+        unpack8(x[2], v0);
+        unpack8(x[3], v1);
+        if (is_k) {
+          const int d1 = r1.x - k0, d2 = r1.z - k0;
+          const bool fast = dtab && __all(d1 >= -kDTab && d1 <= kDTab && d2 >= -kDTab && d2 <= kDTab);
+          float cd[8], sd[8];
+          auto rel = [&](int d) KVX_INLINE {
+            if (fast) {
+              const f32x4* q =
+                  reinterpret_cast<const f32x4*>(rotd + (d + kDTab) * kTabHalf + i0);
+#pragma unroll
+              for (int i = 0; i < 4; ++i) {
+                const f32x4 t = q[i];
+                cd[2 * i] = t[0];
+                sd[2 * i] = t[1];
+                cd[2 * i + 1] = t[2];
+                sd[2 * i + 1] = t[3];
+              }
+            } else {
+#pragma unroll
+              for (int i = 0; i < 8; ++i) rope_cs(fsl[i0 + i], d, cd[i], sd[i]);
+            }
+          };
+          rel(d1);
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            z0[i] = w0 * x0[i] + w1 * (v0[i] * cd[i] + v1[i] * sd[i]);
+            z1[i] = w0 * x1[i] + w1 * (v1[i] * cd[i] - v0[i] * sd[i]);
+          }
+          if (any3) {
+            rel(d2);
+            unpack8(y[0], v0);
+            unpack8(y[1], v1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              z0[i] += w2 * (v0[i] * cd[i] + v1[i] * sd[i]);
+              z1[i] += w2 * (v1[i] * cd[i] - v0[i] * sd[i]);
+            }
+          }
+          for (int e = r0.x + 3; e < r0.x + n; ++e) {
+            const int k = a.col_idx[e];
+            const float w = a.weight[e];
+            unpack8(ld_src<STREAM>(gp + k * a.ss.t), v0);
+            unpack8(ld_src<STREAM>(gp + k * a.ss.t + half), v1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              float c, sn;
+              rope_cs(fsl[i0 + i], k - k0, c, sn);
+              z0[i] += w * (v0[i] * c + v1[i] * sn);
+              z1[i] += w * (v1[i] * c - v0[i] * sn);
+            }
+          }
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            float c, sn;
+            rope_cs(fsl[i0 + i], k0, c, sn);
+            const float y0 = z0[i], y1 = z1[i];
+            z0[i] = y0 * c + y1 * sn;
+            z1[i] = y1 * c - y0 * sn;
+          }
+        } else {
+#pragma unroll
+          for (int i = 0; i < 8; ++i) {
+            z0[i] = w0 * x0[i] + w1 * v0[i];
+            z1[i] = w0 * x1[i] + w1 * v1[i];
+          }
+          if (any3) {
+            unpack8(y[0], v0);
+            unpack8(y[1], v1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              z0[i] += w2 * v0[i];
+              z1[i] += w2 * v1[i];
+            }
+          }
+          for (int e = r0.x + 3; e < r0.x + n; ++e) {
+            const int k = a.col_idx[e];
+            const float w = a.weight[e];
+            unpack8(ld_src<STREAM>(gp + k * a.ss.t), v0);
+            unpack8(ld_src<STREAM>(gp + k * a.ss.t + half), v1);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+              z0[i] += w * v0[i];
+              z1[i] += w * v1[i];
+            }
+          }
+        }
+        if (PREC == kF16) {
+          x[0] = pack8_f16(z0);
+          x[1] = pack8_f16(z1);
+          return;
+        }
+        x[0] = pack8(z0);
+        x[1] = pack8(z1);
+        if (PREC == kBF16X2) {
+          residual8(z0, x[0], v0);
+          residual8(z1, x[1], v1);
+          x[2] = pack8(v0);
+          x[3] = pack8(v1);
+        }
+      };
+      auto hand_over = [&](int c, const uint4 (&x)[kUnits][4]) KVX_INLINE {
+        bf16_t* hi = lds + c * 2 * kPlane + tid / 8 * kLDA + 8 * g;
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+          bf16_t* q = hi + 32 * u * kLDA;
+          *reinterpret_cast<uint4*>(q) = x[u][0];
+          *reinterpret_cast<uint4*>(q + 64) = x[u][1];
+          if (PREC == kBF16X2) {
+            *reinterpret_cast<uint4*>(q + kPlane) = x[u][2];
+            *reinterpret_cast<uint4*>(q + kPlane + 64) = x[u][3];
+          }
+        }
+      };
+      Tile Tg = stT;  // the group being transformed, from its first tile here
+      int ord = 0;    // and that tile's ordinal
+      uint4 xa[kUnits][4], xb[kUnits][4];
+      load_rows(Tg);
+      issue(Tg, 0, xa);
+      if (two) issue(Tg, 1, xb);
+      for (bool first = true;; first = false) {
+        // the steps from s up to ws, where chunk 0 is handed over, are shared
+        // evenly by the group's units (the first group has none)
+        const int s0 = s, ws = first ? 0 : (ord - 1) * spt + 1;
+        auto pace = [&](int done) KVX_INLINE {
+          const int to = s0 + (done * (ws - s0) >> (two ? 3 : 2));
+          while (s < to) end_step();
+        };
+        const bool is_k = Tg.kv == 0;
+        const bf16_t* g0 = chunk_ptr(Tg, 0);
+        const bf16_t* g1 = two ? chunk_ptr(Tg, 1) : g0;
+        issue3(g0, 0);
+#pragma unroll
+        for (int u = 0; u < kUnits; ++u) {
+          unit(xa[u], g0, u, ic[0], is_k);
+          if (u + 1 < kUnits) issue3(g0, u + 1);
+          else if (two) issue3(g1, 0);
+          if (!first && (u + 1 < kUnits || two)) pace(u + 1);
+        }
+        if (first) {
+          hand_over(0, xa);
+          lds_barrier();
+        }
+        if (two) {
+#pragma unroll
+          for (int u = 0; u < kUnits; ++u) {
+            unit(xb[u], g1, u, ic[1], is_k);
+            if (u + 1 < kUnits) {
+              issue3(g1, u + 1);
+              if (!first) pace(kUnits + u + 1);
+            }
+          }
+        }
+        // the next group; K and V of a row tile share its entries
+        const int left = n_tiles - Tg.nt;
+        ord += left;
+        const bool more = ord < ntw;
+        if (more) {
+          for (int i = 0; i < left; ++i) next_tile(Tg);
+          if (Tg.kv == 0) load_rows(Tg);
+        }
+        if (!first) {
+          while (s < ws) end_step();
+          hand_over(0, xa);
+        }
+        if (more) issue(Tg, 0, xa);
+        if (!first) end_step();
+        if (two) {
+          hand_over(1, xb);
+          if (more) issue(Tg, 1, xb);
+          end_step();
+        }
+        if (!more) break;
+      }
+      while (s < nsteps) end_step();
+      return;
+    }
+    // Step in which the chunk at P is written: the step before its use.
+    auto write_step = [&](const ChunkPos& P) KVX_INLINE -> int { return P.ord * spt + P.c - 1; };
     // Transform the next chunk (the one at tpos, written at write_step) from
     // raw set R, and
     // refill R with the chunk kDepth further on.  Called with the sets in turn
     // (chunk mod kDepth), so each set keeps its registers.
     auto produce = [&](int next, Raw& R, const Raw& Rn) KVX_INLINE {
       while (s < write_step(tpos)) end_step();  // steps with nothing to transform
-      bf16_t* buf = lds + (RES ? tpos.c : (s + 1) & 1) * 2 * kPlane;
-      const bool more = next + kDepth < nprod;
+      bf16_t* buf = lds + ((s + 1) & 1) * 2 * kPlane;
+      const bool more = next + kDepth < nchunks;
       const bf16_t* gp = fetch_addr(more);
       transform(R, buf, buf + kPlane);
-      second_issue(Rn, next + 1 < nprod);  // Rn: the chunk after this one
+      second_issue(Rn, next + 1 < nchunks);  // Rn: the chunk after this one
       fetch_issue(gp, R, more);
       end_step();
     };
     int next = 1;
     if constexpr (kDepth == 3) {
-      for (; next + 2 < nprod; next += 3) {
+      for (; next + 2 < nchunks; next += 3) {
         produce(next, rB, rC);
         produce(next + 1, rC, rA);
         produce(next + 2, rA, rB);
       }
-      if (next < nprod) produce(next, rB, rC);
-      if (next + 1 < nprod) produce(next + 1, rC, rA);
+      if (next < nchunks) produce(next, rB, rC);
+      if (next + 1 < nchunks) produce(next + 1, rC, rA);
     } else {
-      for (; next + 1 < nprod; next += 2) {
+      for (; next + 1 < nchunks; next += 2) {
         produce(next, rB, rA);
         produce(next + 1, rA, rB);
       }
-      if (next < nprod) produce(next, rB, rA);
+      if (next < nchunks) produce(next, rB, rA);
     }
     while (s < nsteps) end_step();
     return;

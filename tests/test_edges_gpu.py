@@ -194,3 +194,50 @@ def test_misaligned_layout_refused():
     st = kvx.kvx_translate_status(dev.tr.plan, io, T.cuda.current_stream().cuda_stream)
     assert st == kvx.KVX_EUNSUPPORTED
     dev.close()
+
+
+# (source heads x dim, target heads x dim, mix, tokens, batch, largest span, precision, random map)
+RESIDENT = [
+    ((2, 64), (3, 128), 1, 130, 1, 1, kvx.KVX_PREC_BF16X2, False),    # one chunk, single entries
+    ((2, 128), (8, 64), 1, 517, 5, 5, kvx.KVX_PREC_BF16X2, False),    # fourth and fifth entries
+    ((1, 256), (2, 256), 1, 640, 4, 4, kvx.KVX_PREC_BF16X2, False),   # no rotation table (Ds 256)
+    ((1, 64), (4, 128), 4, 900, 4, 3, kvx.KVX_PREC_F16, False),       # four mixed layers in a row
+    ((2, 128), (4, 256), 1, 700, 3, 6, kvx.KVX_PREC_BF16X2, True),    # entries far apart, empty rows
+    ((4, 32), (5, 64), 2, 2100, 2, 3, kvx.KVX_PREC_BF16X2_OUTLIER, False),
+]
+
+
+@pytest.mark.parametrize("case", RESIDENT, ids=lambda c: f"{c[0]}-{c[1]}-x{c[2]}-{c[3]}x{c[4]}-s{c[5]}-p{c[6]}")
+def test_resident_transform(case):
+    """The resident order's register transform: one and two chunks, several
+    RoPE halves per chunk, spans short of, at and past the entries held in
+    LDS, relative rotations inside and outside the table."""
+    (hs, ds), (ht, dt), mix, tokens, batch, span, prec, rand = case
+    lt = 5
+    spec = _spec(name="resident-transform", src=S.ModelShape(4, hs, ds, 1.0e4),
+                 tgt=S.ModelShape(lt, ht, dt, 5.0e5), mix=mix,
+                 layer_map=tuple((l + j) % 4 for l in range(lt) for j in range(mix)),
+                 src_tokens=tokens, batch=batch, span_lo=1, span_hi=max(span, 2),
+                 outliers=0 if prec == kvx.KVX_PREC_F16 else 2)
+    prob = S.make_problem(spec)
+    if span == 1 or rand:
+        rng = np.random.default_rng(3)
+        tt = np.array([tokens - 7 * b for b in range(batch)], dtype=np.int32)
+        n = rng.integers(0, span + 1, size=int(tt.sum())) if rand else np.ones(int(tt.sum()), int)
+        cols = rng.integers(0, tokens, size=int(n.sum()))
+        prob = dataclasses.replace(
+            prob, tgt_tokens=tt, row_ptr=np.concatenate([[0], np.cumsum(n)]).astype(np.int32),
+            col_idx=cols.astype(np.int32),
+            weight=rng.uniform(-1.0, 1.0, size=len(cols)).astype(np.float32))
+    marks = None
+    if prec == kvx.KVX_PREC_BF16X2_OUTLIER:
+        marks = (S.outlier_channels(spec, 0), S.outlier_channels(spec, 1))
+    dev = U.DevProblem(prob, prec, cap=int(prob.tgt_tokens.max()), outliers=marks)
+    assert dev.tr.info().kernel == 1 and dev.tr.info().tile_order == 2
+    dev.run()
+    U.torch().cuda.synchronize()
+    rk, rv = O.translate(prob, cap=dev.cap)
+    # split operands: 0.5 ulp of rounding and fp32 sums; else the operands'
+    # own rounding, bounded by check_close's envelope
+    U.check_full(dev, rk, rv, spec.name, ulp_bound=0.75 if prec == kvx.KVX_PREC_BF16X2 else None)
+    dev.close()
