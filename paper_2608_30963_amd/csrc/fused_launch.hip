@@ -61,19 +61,36 @@ void launch_p(bool identity, bool ds128, int grid, hipStream_t st, const FusedAr
     launch_ps<PREC, false>(identity, ds128, grid, st, a);
 }
 
+template <int PREC>
+void launch_s(bool identity, int grid, hipStream_t st, const FusedArgs& a) {
+  if (identity)
+    small_kernel<true, PREC><<<dim3(grid), dim3(256), 0, st>>>(a);
+  else
+    small_kernel<false, PREC><<<dim3(grid), dim3(256), 0, st>>>(a);
+}
+
 }  // namespace
 
 #if KVX_LAUNCH_PREC == 0
 void launch_fused_bf16x2(bool identity, bool ds128, int grid, hipStream_t st, const FusedArgs& a) {
   launch_p<kBF16X2>(identity, ds128, grid, st, a);
 }
+void launch_small_bf16x2(bool identity, int grid, hipStream_t st, const FusedArgs& a) {
+  launch_s<kBF16X2>(identity, grid, st, a);
+}
 #elif KVX_LAUNCH_PREC == 1
 void launch_fused_bf16(bool identity, bool ds128, int grid, hipStream_t st, const FusedArgs& a) {
   launch_p<kBF16>(identity, ds128, grid, st, a);
 }
+void launch_small_bf16(bool identity, int grid, hipStream_t st, const FusedArgs& a) {
+  launch_s<kBF16>(identity, grid, st, a);
+}
 #else
 void launch_fused_f16(bool identity, bool ds128, int grid, hipStream_t st, const FusedArgs& a) {
   launch_p<kF16>(identity, ds128, grid, st, a);
+}
+void launch_small_f16(bool identity, int grid, hipStream_t st, const FusedArgs& a) {
+  launch_s<kF16>(identity, grid, st, a);
 }
 #endif
 

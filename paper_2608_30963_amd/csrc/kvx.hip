@@ -407,6 +407,22 @@ void launch_fused(bool identity, bool ds128, int precision, int grid, hipStream_
   }
 }
 
+void launch_small(bool identity, int precision, int grid, hipStream_t st, const FusedArgs& a) {
+  switch (precision) {
+    case KVX_PREC_BF16: launch_small_bf16(identity, grid, st, a); break;
+    case KVX_PREC_F16: launch_small_f16(identity, grid, st, a); break;
+    default: launch_small_bf16x2(identity, grid, st, a); break;
+  }
+}
+
+// The small-call kernel while all of its 32-row workgroups run at once, two on
+// a compute unit.  Measured in us per call (small, persistent) by workgroups,
+// on 256 compute units: [512 -> 256] 224: 14.1, 22.2; 448: 17.5, 22.4; 672:
+// 26.8, 22.9.  [256 -> 1024] spans 416: 15.2, 21.6; 624: 22.0, 22.6; 832: 26.7,
+// 24.8.  [256 -> 1024] identity 448: 14.7, 17.1; 896: 24.1, 16.6.  [3072 -> 512]
+// spans 336: 64, 118; 672: 113, 120.
+bool small_call(const kvx_plan* p, int64_t workgroups) { return workgroups <= 2 * p->n_cu; }
+
 // The general kernel for one group of contexts.
 template <typename T>
 void launch_tiled(const kvx_plan* p, const Strides& ss, const Strides& ts, const char* sk,
@@ -635,7 +651,14 @@ extern "C" kvx_status kvx_translate(const kvx_plan* p, const kvx_io* io_in, void
     const int nb = static_cast<int>(B - b0 < kMaxBatch ? B - b0 : kMaxBatch);
     BatchArgs ba{};
     ba.n = nb;
-    const int rows_per_tile = fused ? kMT : kGRows;
+    const int n_tiles = fused ? (p->dout / 64 + 3) / 4 : 0;
+    bool small = false;
+    if (fused) {
+      int64_t rt = 0;
+      for (int i = 0; i < nb; ++i) rt += (ttok[b0 + i] + kSRows - 1) / kSRows;
+      small = small_call(p, rt * n_tiles * 2 * Lt);
+    }
+    const int rows_per_tile = small ? kSRows : fused ? kMT : kGRows;
     int tiles = 0;
     for (int i = 0; i < nb; ++i) {
       ba.tile_start[i] = tiles;
@@ -684,7 +707,7 @@ extern "C" kvx_status kvx_translate(const kvx_plan* p, const kvx_io* io_in, void
       a.row_ptr = io.row_ptr;
       a.col_idx = io.col_idx;
       a.weight = io.weight;
-      a.n_tiles = (p->dout / 64 + 3) / 4;
+      a.n_tiles = n_tiles;
       a.row_tiles = tiles;
       a.pg = pg;
       a.split_mask = p->split_mask;
@@ -699,7 +722,10 @@ extern "C" kvx_status kvx_translate(const kvx_plan* p, const kvx_io* io_in, void
       // persistent: one workgroup per compute unit (the kernel's LDS use
       // allows exactly one)
       const int grid = static_cast<int>(total < p->n_cu ? total : p->n_cu);
-      launch_fused(identity, Ds == 128, p->precision, grid, st, a);
+      if (small)
+        launch_small(identity, p->precision, static_cast<int>(total), st, a);
+      else
+        launch_fused(identity, Ds == 128, p->precision, grid, st, a);
     } else if (p->dtype == KVX_F32) {
       launch_tiled<float>(p, ss, ts, sk, sv, tk, tv, io, identity, pg, ba, tiles, st);
     } else {

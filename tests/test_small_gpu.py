@@ -1,0 +1,78 @@
+"""The small-call kernel (32-row tiles, segments of four chunks, two with
+spans) and the persistent kernel on the same shapes, against the oracle.  The
+call's size alone selects the kernel: at most two 32-row workgroups per
+compute unit run the small one, so the second batch size of each case is past
+that."""
+import numpy as np
+import pytest
+
+from oracle import oracle as O
+from paper_2608_30963_amd import kvx, synth as S
+
+from . import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+X2, F16, OUT = kvx.KVX_PREC_BF16X2, kvx.KVX_PREC_F16, kvx.KVX_PREC_BF16X2_OUTLIER
+
+# (heads x dim) source, target, mix, tokens, largest span, precision, small batch, large batch
+CASES = [
+    ((1, 128), (1, 64), 1, 1, 0, X2, 1, 60),     # smallest of everything
+    ((4, 128), (2, 128), 1, 33, 0, X2, 2, 30),   # four chunks, one row past a tile
+    ((4, 128), (2, 128), 1, 33, 0, F16, 2, 30),
+    ((5, 128), (3, 128), 1, 31, 0, X2, 1, 30),   # a second segment of one chunk, half an N tile
+    ((8, 128), (5, 64), 1, 64, 0, X2, 1, 15),    # two whole segments, two N tiles, the second of one block
+    ((8, 32), (1, 256), 1, 40, 0, X2, 1, 30),    # four heads a chunk
+    ((1, 256), (2, 128), 3, 65, 0, OUT, 1, 20),  # half a head a chunk, three mixed layers
+    ((2, 64), (1, 128), 1, 70, 4, X2, 2, 60),    # spans past the two held entries
+    ((3, 128), (4, 128), 1, 50, 2, X2, 1, 20),   # a second segment of one chunk, spans
+    ((1, 256), (2, 512), 2, 90, 3, F16, 1, 10),  # angles afresh each chunk, spans
+]
+
+
+@pytest.mark.parametrize("paged", [False, True], ids=["", "paged"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}-{c[1]}-x{c[2]}-{c[3]}-s{c[4]}-p{c[5]}")
+def test_small_and_persistent_kernels(case, paged):
+    (hs, ds), (ht, dt), mix, tokens, span, prec, small, large = case
+    T = G.torch()
+    lt = 5
+    n_cu = T.cuda.get_device_properties(0).multi_processor_count
+    for batch in (small, large):
+        spec = S.Spec(330, "small", S.ModelShape(4, hs, ds, 1.0e4), S.ModelShape(lt, ht, dt, 5.0e5),
+                      mix, tuple((l + j) % 4 for l in range(lt) for j in range(mix)), S.BF16, tokens,
+                      batch=batch, outliers=0 if prec == F16 else 2, bias_std=0.3,
+                      span_lo=1 if span else 0, span_hi=span)
+        prob = S.make_problem(spec)
+        marks = (S.outlier_channels(spec, 0), S.outlier_channels(spec, 1)) if prec == OUT else None
+        cap = int(prob.tgt_tokens.max())
+        dev = G.DevProblem(prob, prec, cap=cap, outliers=marks)
+        assert dev.tr.info().kernel == 1
+        wgs = sum(-(-int(t) // 32) for t in prob.tgt_tokens) * -(-ht * dt // 256) * 2 * lt
+        assert (wgs <= 2 * n_cu) == (batch == small), (wgs, n_cu)
+        print(f"[small] {case} batch {batch} paged {paged}", flush=True)
+        if paged:
+            bs = 16
+            per = -(-cap // bs)
+            table = np.random.default_rng(1).permutation(batch * per).astype(np.int32).reshape(batch, per)
+            pk = T.full((lt, batch * per, ht, bs, dt), float("nan"), dtype=T.bfloat16, device="cuda")
+            pv = T.full_like(pk, float("nan"))
+            ident = prob.row_ptr is None
+            dev.tr(dev.src_k, dev.src_v, pk, pv, cap, None if ident else prob.tgt_tokens,
+                   dev.row_ptr, dev.col_idx, dev.weight, block_table=T.from_numpy(table).cuda(),
+                   block_size=bs)
+            T.cuda.synchronize()
+            idx = T.from_numpy(table.reshape(-1).astype(np.int64)).cuda()
+            for pages, out in ((pk, dev.tgt_k), (pv, dev.tgt_v)):
+                rows = pages[:, idx].view(lt, batch, per, ht, bs, dt).permute(0, 1, 3, 2, 4, 5)
+                out.copy_(rows.reshape(lt, batch, ht, per * bs, dt)[:, :, :, :cap])
+        else:
+            dev.run()
+        T.cuda.synchronize()
+        rk, rv = O.translate(prob, cap=cap)
+        # split operands: 0.5 ulp of rounding and fp32 sums; else the operands'
+        # own rounding, within check_close's envelope
+        G.check_full(dev, rk, rv, f"batch {batch}", ulp_bound=0.75 if prec == X2 else None)
+        gk = G.dev_to_f64(dev.tgt_k, spec.dtype)
+        for b, t in enumerate(prob.tgt_tokens):
+            assert np.isnan(gk[:, b, :, int(t):]).all(), "row past the context's end was written"
+        dev.close()
