@@ -647,17 +647,17 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
 
     float csc[CS_CACHE ? kUnits : 1][8], css[CS_CACHE ? kUnits : 1][8];
 
-    // Span map, contiguous target: second-entry data of the chunk at tpos
-    // (the next one to be transformed), requested at the end of the previous
-    // chunk's transform so that a whole step covers its latency.  (The paged
-    // variant, which holds its block ids as well, reads second entries in
-    // the transform like later ones: the prefetch would spill there.)
-    constexpr bool kPrefetch2 = !IDENT && !PAGED;
-    uint4 yb0[kPrefetch2 ? kUnits : 1], yb1[kPrefetch2 ? kUnits : 1];
-    float ybw[kPrefetch2 ? kUnits : 1];  // its pooling weight (0: no second entry)
-    int ybk[kPrefetch2 ? kUnits : 1];    // and source token
+    // Span map: second-entry data of the chunk at tpos (the next one to be
+    // transformed), requested at the end of the previous chunk's transform so
+    // that a whole step covers its latency.  (Paged targets once read second
+    // entries in the transform, when the producers still held the block ids:
+    // 28 layers [3072 -> 512], spans of 1-2, 8192 tokens 3.01 -> 2.22 ms, 26
+    // layers [512 -> 1024], spans of 1-3, 4096 tokens 0.595 -> 0.442 ms.)
+    uint4 yb0[IDENT ? 1 : kUnits], yb1[IDENT ? 1 : kUnits];
+    float ybw[IDENT ? 1 : kUnits];  // its pooling weight (0: no second entry)
+    int ybk[IDENT ? 1 : kUnits];    // and source token
     auto second_issue = [&](const Raw& R, bool exists) KVX_INLINE {
-      if constexpr (kPrefetch2) {
+      if constexpr (!IDENT) {
         const bf16_t* gp = group_ptr(tpos);
         // the second entries' tokens and weights are those of the tile:
         // (re)read at its first chunk only
@@ -719,9 +719,9 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
       // span maps: the token and weight of each row's third entry, when it
       // has one, requested before any row's arithmetic (the entry's data is
       // then requested in the row's turn without a dependent index load)
-      int k3[kPrefetch2 ? kUnits : 1];
-      float w3[kPrefetch2 ? kUnits : 1];
-      if constexpr (kPrefetch2) {
+      int k3[IDENT ? 1 : kUnits];
+      float w3[IDENT ? 1 : kUnits];
+      if constexpr (!IDENT) {
 #pragma unroll
         for (int u = 0; u < kUnits; ++u) {
           k3[u] = 0;
@@ -736,7 +736,7 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
       for (int u = 0; u < kUnits; ++u) {
         const int r = tid / 8 + 32 * u;
         float z0[8], z1[8];
-        if constexpr (kPrefetch2) {
+        if constexpr (!IDENT) {
           // First two entries.  For K they are pooled in the first entry's
           // frame, R(-k0) (w0 x_k0 + w1 R(-(k1 - k0)) x_k1) -- equal to
           // w0 R(-k0) x_k0 + w1 R(-k1) x_k1 -- so only the first entry needs
@@ -782,8 +782,7 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
           float x0[8], x1[8];
           unpack8(R.x0[u], x0);
           unpack8(R.x1[u], x1);
-          const int k = IDENT ? T.t0 + r : R.ri.k0[u];
-          const float w = IDENT ? 1.f : R.ri.w0[u];
+          const int k = T.t0 + r;
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             float y0 = x0[i], y1 = x1[i];
@@ -798,15 +797,15 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
               y0 = x0[i] * cs_ + x1[i] * sn;
               y1 = x1[i] * cs_ - x0[i] * sn;
             }
-            z0[i] = w * y0;
-            z1[i] = w * y1;
+            z0[i] = y0;
+            z1[i] = y1;
           }
         }
         if constexpr (!IDENT) {
-          for (int e = R.ri.e0[u] + (kPrefetch2 ? 2 : 1); e < R.ri.e1[u]; ++e) {
-            const bool third = kPrefetch2 && e == R.ri.e0[u] + 2;
-            const int k = third ? k3[kPrefetch2 ? u : 0] : a.col_idx[e];
-            const float w = third ? w3[kPrefetch2 ? u : 0] : a.weight[e];
+          for (int e = R.ri.e0[u] + 2; e < R.ri.e1[u]; ++e) {
+            const bool third = e == R.ri.e0[u] + 2;
+            const int k = third ? k3[u] : a.col_idx[e];
+            const float w = third ? w3[u] : a.weight[e];
             const bf16_t* p = pg.p + k * a.ss.t;
             float x0[8], x1[8];
             unpack8(ld_src<STREAM>(p), x0);

@@ -27,6 +27,7 @@ CASES = [
     ((2, 64), (1, 128), 1, 70, 4, X2, 2, 60),    # spans past the two held entries
     ((3, 128), (4, 128), 1, 50, 2, X2, 1, 20),   # a second segment of one chunk, spans
     ((1, 256), (2, 512), 2, 90, 3, F16, 1, 10),  # angles afresh each chunk, spans
+    ((8, 128), (2, 128), 1, 90, 3, X2, 1, 40),   # the interleaved order, spans
 ]
 
 
