@@ -226,6 +226,16 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Orders LDS accesses of the lanes of one wave for the compiler: what a lane
+// stored before it is what the others read after it, and the reverse.  The
+// wave barrier keeps the lanes together; neither costs an instruction that
+// waits for other waves or for global loads.
+__device__ __forceinline__ void wave_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 __device__ __forceinline__ void unpack8(const uint4 v, float* x) {
   const uint32_t w[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
@@ -943,7 +953,9 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
                ic[c];
       };
       // Entries of T's rows.  A wave fills the 32 rows that its own threads
-      // transform, so no barrier is needed.  Unconditional loads: a row past
+      // transform, and its LDS operations run in order, so no barrier is
+      // needed; the wave fences keep the compiler from moving a lane's reads
+      // across the stores of the other lanes.  Unconditional loads: a row past
       // the context's end reads the last row's pointers and has no entries,
       // an absent entry reads the zero sink (weight 0) and keeps the first
       // one's token.
@@ -962,10 +974,12 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
           w[e] = *(n > e ? reinterpret_cast<const int32_t*>(a.weight) + e0 + e : zi);
           if (e > 0) k[e] = n > e ? k[e] : k[0];
         }
+        wave_fence();
         if (tid % 64 < 32) {
           rinf[r][0] = make_int4(e0, n, k[0], w[0]);
           rinf[r][1] = make_int4(k[1], w[1], k[2], w[2]);
         }
+        wave_fence();
       };
       // first and second entries of every unit of chunk c
       auto issue = [&](const Tile& T, int c, uint4 (&x)[kUnits][4]) KVX_INLINE {
