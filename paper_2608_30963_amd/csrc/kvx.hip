@@ -8,6 +8,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <new>
+#include <tuple>
 #include <vector>
 
 #include "kvx.h"
@@ -38,6 +39,9 @@ enum Kernel { kTiled = 0, kFused = 1 };
 kvx_status kvx::hip_status(hipError_t e) {
   if (e == hipSuccess) return KVX_OK;
   g_last_hip = static_cast<int32_t>(e);
+  // the runtime keeps an error until it is read: reported here, it must not be
+  // taken for a later call's
+  (void)hipGetLastError();
   return e == hipErrorOutOfMemory ? KVX_ENOMEM : KVX_EHIP;
 }
 
@@ -187,6 +191,19 @@ __global__ void __launch_bounds__(256) pack_fused(const uint16_t* w, uint16_t* o
   }
 }
 
+// Launch on the default stream with the launch's own status (the runtime's
+// last error may be one that the caller's other HIP calls left).
+template <typename... P, typename... A>
+hipError_t launch(void (*kernel)(P...), dim3 grid, A... a) {
+  std::tuple<P...> params(static_cast<P>(a)...);
+  return std::apply(
+      [&](auto&... p) {
+        void* args[] = {&p...};
+        return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, dim3(256), args, 0, nullptr);
+      },
+      params);
+}
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
@@ -309,19 +326,17 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   const dim3 pgrid(static_cast<unsigned>(std::min<size_t>(8192, (size_t(lt) * pelems / 4 + 255) / 256)));
   for (int kv = 0; kv < 2; ++kv) {
     if (p->kernel == kFused)
-      pack_fused<<<pgrid, dim3(256)>>>(static_cast<const uint16_t*>(wsrc[kv]),
-                                       static_cast<uint16_t*>(p->w[kv]),
-                                       static_cast<uint16_t*>(p->wh[kv]), bad, int(lt), p->din,
-                                       p->dout, d->src.head_dim);
+      e = launch(pack_fused, pgrid, static_cast<const uint16_t*>(wsrc[kv]),
+                 static_cast<uint16_t*>(p->w[kv]), static_cast<uint16_t*>(p->wh[kv]), bad, lt,
+                 p->din, p->dout, d->src.head_dim);
     else if (esz == 4)
-      pack_tiled<float><<<pgrid, dim3(256)>>>(
-          static_cast<const float*>(wsrc[kv]), static_cast<float*>(p->w[kv]), int(lt), p->din,
-          p->dout, d->src.head_dim, d->tgt.head_dim, tiled_npb(dout64), tiled_nch(din64) * kGQ);
+      e = launch(pack_tiled<float>, pgrid, static_cast<const float*>(wsrc[kv]),
+                 static_cast<float*>(p->w[kv]), lt, p->din, p->dout, d->src.head_dim,
+                 d->tgt.head_dim, tiled_npb(dout64), tiled_nch(din64) * kGQ);
     else
-      pack_tiled<bf16_t><<<pgrid, dim3(256)>>>(
-          static_cast<const bf16_t*>(wsrc[kv]), static_cast<bf16_t*>(p->w[kv]), int(lt), p->din,
-          p->dout, d->src.head_dim, d->tgt.head_dim, tiled_npb(dout64), tiled_nch(din64) * kGQ);
-    e = hipGetLastError();
+      e = launch(pack_tiled<bf16_t>, pgrid, static_cast<const bf16_t*>(wsrc[kv]),
+                 static_cast<bf16_t*>(p->w[kv]), lt, p->din, p->dout, d->src.head_dim,
+                 d->tgt.head_dim, tiled_npb(dout64), tiled_nch(din64) * kGQ);
     if (e != hipSuccess) return fail(hip_fail(e));
   }
   if (want_f16) {

@@ -92,3 +92,23 @@ def test_injected_launch_fault_staged(fault_env):
     U.check_full(dev, rk, rv, "staged after fault", 0.75)
     del keep
     dev.close()
+
+
+def test_a_failed_plan_leaves_the_next_calls_alone():
+    """A plan whose weights exceed the device's memory is refused with
+    KVX_ENOMEM before its weights are read; the error ends with that call:
+    the next plan is made, and a translation with it runs."""
+    spec = S.config(2, src_tokens=40)
+    prob = S.make_problem(spec)
+    w = U.np_to_dev(prob.w_k, spec.dtype)
+    big = S.ModelShape(1, 1024, 128, 1.0e4)   # 64 layers of [131072 -> 131072]: 4.4e12 bytes
+    print("[fault] plan past the device's memory", flush=True)
+    with pytest.raises(kvx.KvxError) as err:
+        kvx.kvx_plan_create(big, S.ModelShape(64, 1024, 128, 1.0e4), 1, [0] * 64, kvx.KVX_BF16, w, w)
+    assert err.value.status == kvx.KVX_ENOMEM
+    dev = U.DevProblem(prob)
+    dev.run()
+    U.torch().cuda.synchronize()
+    rk, rv = O.translate(prob, cap=dev.cap)
+    U.check_full(dev, rk, rv, "after a failed plan", 0.75)
+    dev.close()
