@@ -98,7 +98,8 @@ typedef struct {
                                 input feature (j*Hs + h)*Ds + d of target layer l
                                 is source layer layer_map[l*mix+j], head h, dim d */
   int32_t dtype;             /* kvx_dtype of KV tensors and weights */
-  const void* w_k;           /* device [Lt][Ht*Dt][mix*Hs*Ds], nn.Linear [out][in] order */
+  const void* w_k;           /* device [Lt][Ht*Dt][mix*Hs*Ds], nn.Linear [out][in] order
+                                (or pinned host memory, or another GPU's: copied) */
   const void* w_v;
   const float* b_k;          /* device fp32 [Lt][Ht*Dt], or NULL for zero bias */
   const float* b_v;

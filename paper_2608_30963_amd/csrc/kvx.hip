@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <new>
 #include <tuple>
 #include <vector>
@@ -204,6 +205,34 @@ hipError_t launch(void (*kernel)(P...), dim3 grid, A... a) {
       params);
 }
 
+// The caller's weights as kernels of device `dev` may read them: in place when
+// they lie in its memory, else (pinned host or managed memory, another GPU's)
+// copied through the host to *staged, which the caller frees.  An allocation
+// that ends before the weights do is refused here, memory unknown to the
+// runtime by the copy.
+hipError_t local_weights(const void* w, size_t bytes, int dev, const void** out, void** staged) {
+  *staged = nullptr;
+  hipPointerAttribute_t at{};
+  hipError_t e = hipPointerGetAttributes(&at, w);
+  if (e == hipSuccess && at.type == hipMemoryTypeDevice && at.device == dev) {
+    hipDeviceptr_t base = nullptr;
+    size_t size = 0;
+    e = hipMemGetAddressRange(&base, &size, const_cast<void*>(w));
+    if (e != hipSuccess) return e;
+    const size_t off = static_cast<const char*>(w) - static_cast<const char*>(base);
+    *out = w;
+    return off + bytes <= size ? hipSuccess : hipErrorInvalidValue;
+  }
+  if (e != hipSuccess) (void)hipGetLastError();  // handled: the copy decides
+  const std::unique_ptr<char[]> host(new (std::nothrow) char[bytes]);
+  if (!host) return hipErrorOutOfMemory;
+  e = hipMemcpy(host.get(), w, bytes, hipMemcpyDeviceToHost);
+  if (e == hipSuccess) e = hipMalloc(staged, bytes);
+  if (e == hipSuccess) e = hipMemcpy(*staged, host.get(), bytes, hipMemcpyHostToDevice);
+  *out = *staged;
+  return e;
+}
+
 size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
 }  // namespace
@@ -317,12 +346,23 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   e = hipMemset(p->zsink, 0, kSinkBytes);
   if (e != hipSuccess) return fail(hip_fail(e));
 
-  // Weights: packed on the device, straight from the caller's buffers (the
-  // trash area serves as the fp16 range flag until the plan is used).
+  // Weights: packed on the device (the trash area serves as the fp16 range
+  // flag until the plan is used).
   int32_t* bad = static_cast<int32_t*>(p->trash);
   e = hipMemset(bad, 0, sizeof *bad);
   if (e != hipSuccess) return fail(hip_fail(e));
   const void* wsrc[2] = {d->w_k, d->w_v};
+  struct Staged {
+    void* p[2] = {nullptr, nullptr};
+    ~Staged() {
+      for (void* q : p)
+        if (q) (void)hipFree(q);  // waits for the pack kernels
+    }
+  } staged;
+  for (int kv = 0; kv < 2; ++kv) {
+    e = local_weights(wsrc[kv], size_t(lt) * dout64 * din64 * esz, p->device, &wsrc[kv], &staged.p[kv]);
+    if (e != hipSuccess) return fail(hip_fail(e));
+  }
   const dim3 pgrid(static_cast<unsigned>(std::min<size_t>(8192, (size_t(lt) * pelems / 4 + 255) / 256)));
   for (int kv = 0; kv < 2; ++kv) {
     if (p->kernel == kFused)

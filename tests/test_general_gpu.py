@@ -7,7 +7,7 @@ ones that reach the groups."""
 import pytest
 
 from oracle import oracle as O
-from paper_2608_30963_amd import synth as S
+from paper_2608_30963_amd import kvx, synth as S
 
 from . import gpu_util as G
 
@@ -43,4 +43,39 @@ def test_general_kernel_tile_edges(case):
     rk, rv = O.translate(prob)
     # bf16: correct rounding is 0.5 ulp, fp32 sums below it add under 0.01
     G.check_full(dev, rk, rv, "general", ulp_bound=0.6)
+    dev.close()
+
+
+@pytest.mark.parametrize("dtype,prec", [(S.F32, kvx.KVX_PREC_BF16X2), (S.BF16, kvx.KVX_PREC_BF16X2),
+                                        (S.BF16, kvx.KVX_PREC_F16)])
+def test_plan_weights_by_memory_kind(dtype, prec):
+    """Weights in pinned host memory give the plan that device weights give;
+    pageable host memory, and device memory that ends before the weights do,
+    are refused on the host."""
+    T = G.torch()
+    spec = S.Spec(311, "weights", S.ModelShape(2, 2, 128, 1.0e4), S.ModelShape(2, 1, 128, 5.0e5),
+                  1, (1, 0), dtype, 70, batch=1, bias_std=0.2)
+    prob = S.make_problem(spec)
+    dev = G.DevProblem(prob, prec)
+    dev.run()
+    want_k, want_v = dev.tgt_k.clone(), dev.tgt_v.clone()
+    host = [w.cpu() for w in (dev.w_k, dev.w_v)]
+
+    def plan(w_k, w_v):
+        return kvx.Translator(spec.src, spec.tgt, spec.mix, spec.layer_map, dev.kdtype, w_k, w_v,
+                              dev.b_k, dev.b_v, precision=prec)
+    dev.tr.close()
+    dev.tr = plan(host[0].pin_memory(), host[1].pin_memory())
+    dev.tgt_k.fill_(0)
+    dev.tgt_v.fill_(0)
+    dev.run()
+    T.cuda.synchronize()
+    assert T.equal(dev.tgt_k, want_k) and T.equal(dev.tgt_v, want_v)
+    nbytes = host[0].numel() * host[0].element_size()
+    block = T.empty(64 << 20, dtype=T.uint8, device="cuda")   # an allocation of its own
+    end = block.data_ptr() + block.numel()
+    for bad_k, bad_v in ((host[0], dev.w_v), (dev.w_k, host[1]), (dev.w_k, end - nbytes + 16)):
+        with pytest.raises(kvx.KvxError) as err:
+            plan(bad_k, bad_v)
+        assert err.value.status == kvx.KVX_EHIP
     dev.close()
