@@ -6,7 +6,9 @@
 // add), for bf16 storage too, whose values are widened exactly.
 //
 // One workgroup owns (target layer l, K|V, context b, kGRows target rows, up
-// to four pair blocks of outputs).  A pair block is 32 consecutive entries of
+// to four pair blocks of outputs).  SHARE: the rows of all contexts are tiled
+// as one list, so that contexts of a few rows share a tile instead of padding
+// one each.  A pair block is 32 consecutive entries of
 // the flattened (target head, i < Dt/2) list: the outputs i and their RoPE
 // partners i + Dt/2, which the two accumulators of a wave hold in the same
 // lane, so the target rotation needs no exchange.  The contraction runs over
@@ -33,7 +35,9 @@
 // stride of din (in brackets): 28 layers of [512 -> 256] at 1024 tokens fp32
 // 0.166 ms, 91 TFLOP/s of the 154 a large fp32 product reaches [5.8 ms]; 24
 // layers of [640 -> 320] at head_dim 80, 1024 tokens bf16 0.27 ms [4.6 ms];
-// 4 layers of [128 -> 128] at 256 tokens fp32 10.7 us a call [34.7 us].
+// 4 layers of [128 -> 128] at 256 tokens fp32 10.7 us a call [34.7 us].  64
+// contexts of one token (SHARE, in brackets a tile each): 28 layers of [512 ->
+// 256] fp32 29 us [269 us], 24 of [640 -> 320] bf16 36 us [443 us].
 #pragma once
 
 #include "common.h"
@@ -51,7 +55,7 @@ struct TiledArgs {
   Strides ss;
   T* tgt[2];                // target K, V
   Strides ts;
-  const T* w[2];            // packed [Lt][npb][nch * kGQ][2][64 lanes][4] (tiled_feature)
+  const T* w[2];            // packed [Lt][npb][nch * kGQ][2][64 lanes][4] (pack_tiled)
   const float* bias[2];     // [Lt][dout] (zeros when the translator has none)
   const int32_t* layer_map; // [Lt][mix]
   int32_t mix, hs, ds, ht, dt, din, dout;
@@ -65,8 +69,17 @@ struct TiledArgs {
   int32_t npb, nch;         // pair blocks of the output, chunks of the contraction
   int32_t group;            // pair blocks per workgroup: 4 (with a remainder of 2, 1) or 1
   Paging pg;                // optional paged target layout
-  BatchArgs ba;
+  BatchArgs ba;             // SHARE: tile_start holds the contexts' first rows in the list
 };
+
+// Context and position of row `row` of the list of all contexts' rows
+// (position -1 past its end).
+__device__ __forceinline__ int2 list_row(const BatchArgs& ba, int row) {
+  int2 r = make_int2(0, row);
+  for (int b = 1; b < ba.n; ++b)
+    if (ba.tile_start[b] <= row) r = make_int2(b, row - ba.tile_start[b]);
+  return row < ba.tile_start[ba.n] ? r : make_int2(0, -1);
+}
 
 // Workgroups along the output: whole groups of four pair blocks, then the
 // remainder as 2 and 1, so that every wave of every workgroup has work.
@@ -81,9 +94,10 @@ __device__ __forceinline__ f32x4 load_w4(const bf16_t* p) {
                __uint_as_float(r.y << 16), __uint_as_float(r.y & 0xffff0000u)};
 }
 
-template <typename T>
+template <typename T, bool SHARE>
 __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
   __shared__ __attribute__((aligned(16))) float z[2][kGRows * kGLD];
+  __shared__ int2 rowi[SHARE ? kGRows : 1];  // the rows' contexts and positions
   // each XCD takes a contiguous range of workgroups, row tiles fastest, so
   // the workgroups that share a layer's weights share an L2
   const int64_t total = static_cast<int64_t>(gridDim.x) * gridDim.y;
@@ -102,9 +116,18 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
     pb0 = nt <= full ? 4 * nt : 4 * full + 2;
     nb = nt < full ? 4 : (nt == full && a.npb % 4 >= 2 ? 2 : 1);
   }
-  const int b = find_context(a.ba, rt);
-  const int t0 = (rt - a.ba.tile_start[b]) * kGRows;
-  const int tt = a.ba.t_tgt[b];
+  const int b = SHARE ? 0 : find_context(a.ba, rt);
+  const int t0 = SHARE ? 0 : (rt - a.ba.tile_start[b]) * kGRows;
+  const int tt = SHARE ? 0 : a.ba.t_tgt[b];
+  if constexpr (SHARE) {
+    if (threadIdx.x < kGRows) rowi[threadIdx.x] = list_row(a.ba, rt * kGRows + threadIdx.x);
+    __syncthreads();
+  }
+  // context and position of row r of the tile (position -1: none)
+  auto row_at = [&](int r) __attribute__((always_inline)) -> int2 {
+    if constexpr (SHARE) return rowi[r];
+    return make_int2(b, t0 + r < tt ? t0 + r : -1);
+  };
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hd = a.ds / 2;
@@ -114,17 +137,21 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
   // this wave's rows of the tile: w + 4 i
   constexpr int kR = kGRows / 4;
   int e0[kR], e1[kR], k0[kR];
+  int ctx[SHARE ? kR : 1];
   float w0[kR];
 #pragma unroll
   for (int i = 0; i < kR; ++i) {
-    const int t = t0 + w + 4 * i;
+    const int2 ri = row_at(w + 4 * i);
+    const int t = SHARE ? __builtin_amdgcn_readfirstlane(ri.y) : ri.y;
+    const int c = SHARE ? __builtin_amdgcn_readfirstlane(ri.x) : b;
+    if constexpr (SHARE) ctx[i] = c;
     e0[i] = 0;
-    e1[i] = t < tt ? 1 : 0;
+    e1[i] = t >= 0 ? 1 : 0;
     k0[i] = t;
     w0[i] = 1.f;
-    if (!a.identity && t < tt) {
-      e0[i] = a.row_ptr[a.ba.row_base[b] + t];
-      e1[i] = a.row_ptr[a.ba.row_base[b] + t + 1];
+    if (!a.identity && t >= 0) {
+      e0[i] = a.row_ptr[a.ba.row_base[c] + t];
+      e1[i] = a.row_ptr[a.ba.row_base[c] + t + 1];
       if (e1[i] > e0[i]) {
         k0[i] = a.col_idx[e0[i]];
         w0[i] = a.weight[e0[i]];
@@ -132,8 +159,14 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
     }
   }
 
-  // the lane's pair of a chunk: its first member at token 0 (nullptr past the
-  // last pair) and its frequency.  First entries are loaded unconditionally (a
+  // source element offset of token k of row i's context
+  auto token = [&](int i, int k) __attribute__((always_inline)) -> int64_t {
+    if constexpr (SHARE) return ctx[i] * a.ss.b + k * a.ss.t;
+    return k * a.ss.t;
+  };
+
+  // the lane's pair of a chunk: its first member at token 0 (SHARE: of context
+  // 0; nullptr past the last pair) and its frequency.  First entries are loaded unconditionally (a
   // load inside a branch makes the compiler drain every load in flight at the
   // merge): lanes and rows without one read the frequency table, whose 8 Ds/2
   // bytes hold both members, and are cleared.
@@ -149,7 +182,7 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
     f = kv == 0 ? a.fs[i] : 0.0;
 #pragma unroll
     for (int r = 0; r < kR; ++r) {
-      const T* p = ok && e1[r] > e0[r] ? xp + k0[r] * a.ss.t : reinterpret_cast<const T*>(a.fs);
+      const T* p = ok && e1[r] > e0[r] ? xp + token(r, k0[r]) : reinterpret_cast<const T*>(a.fs);
       x0[r] = p[0];
       x1[r] = p[hd];
     }
@@ -171,7 +204,7 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
         for (int e = e0[r] + 1; e < e1[r]; ++e) {
           const int k = a.col_idx[e];
           const float we = a.weight[e];
-          const T* p = xp + k * a.ss.t;
+          const T* p = xp + token(r, k);
           y0 = load_f32(p);
           y1 = load_f32(p + hd);
           if (kv == 0) {
@@ -270,8 +303,9 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
   T* dst = a.tgt[kv] + l * a.ts.l + h * a.ts.h + i;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
-    const int t = t0 + 8 * (v / 4) + 4 * (lane / 32) + v % 4;
-    if (t >= tt) continue;
+    const int2 ri = row_at(8 * (v / 4) + 4 * (lane / 32) + v % 4);
+    const int t = ri.y;
+    if (t < 0) continue;
     float u0 = acc0[v] + b0, u1 = acc1[v] + b1;
     if (kv == 0) {
       float cs, sn;
@@ -280,8 +314,8 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
       u0 = y0;
       u1 = y1;
     }
-    const int32_t blk = a.pg.table ? a.pg.table[b * a.pg.max_blocks + t / a.pg.block_size] : 0;
-    T* q = dst + target_row(a.pg, a.ts, b, t, blk);
+    const int32_t blk = a.pg.table ? a.pg.table[ri.x * a.pg.max_blocks + t / a.pg.block_size] : 0;
+    T* q = dst + target_row(a.pg, a.ts, ri.x, t, blk);
     q[0] = store_cvt<T>(u0);
     q[ht2] = store_cvt<T>(u1);
   }

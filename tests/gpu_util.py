@@ -105,6 +105,30 @@ class DevProblem:
         self.tr.close()
 
 
+def run_paged(dev: DevProblem, bs: int = 16):
+    """``dev.run()`` into a paged target cache of ``bs`` tokens a block, blocks
+    in a drawn order, gathered into ``dev.tgt_k`` / ``dev.tgt_v``."""
+    T = torch()
+    prob, spec = dev.prob, dev.spec
+    t, batch = spec.tgt, spec.batch
+    per = -(-dev.cap // bs)
+    table = np.random.default_rng(1).permutation(batch * per).astype(np.int32).reshape(batch, per)
+    pk = T.full((t.n_layers, batch * per, t.n_kv_heads, bs, t.head_dim), float("nan"),
+                dtype=dev.tgt_k.dtype, device="cuda")
+    pv = T.full_like(pk, float("nan"))
+    ident = prob.row_ptr is None
+    dev.tr(dev.src_k, dev.src_v, pk, pv, dev.cap, None if ident else prob.tgt_tokens,
+           dev.row_ptr, dev.col_idx, dev.weight, block_table=T.from_numpy(table).cuda(),
+           block_size=bs)
+    T.cuda.synchronize()
+    idx = T.from_numpy(table.reshape(-1).astype(np.int64)).cuda()
+    for pages, out in ((pk, dev.tgt_k), (pv, dev.tgt_v)):
+        rows = pages[:, idx].view(t.n_layers, batch, per, t.n_kv_heads, bs, t.head_dim)
+        rows = rows.permute(0, 1, 3, 2, 4, 5)
+        out.copy_(rows.reshape(t.n_layers, batch, t.n_kv_heads, per * bs,
+                               t.head_dim)[:, :, :, :dev.cap])
+
+
 def bf16_ulp(x: np.ndarray) -> np.ndarray:
     """Spacing of bfloat16 numbers at |x| (8 significant bits; subnormal
     spacing 2^-133 below the smallest normal 2^-126)."""

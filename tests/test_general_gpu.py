@@ -4,6 +4,9 @@ tile) at the edges of its tiles, against the oracle: 32-row tiles, chunks of
 split the contraction when fewer than four.  A workgroup takes one pair block
 while larger groups would leave compute units idle, so the long cases are the
 ones that reach the groups."""
+import dataclasses
+
+import numpy as np
 import pytest
 
 from oracle import oracle as O
@@ -46,6 +49,42 @@ def test_general_kernel_tile_edges(case):
     dev.close()
 
 
+@pytest.mark.parametrize("paged", [False, True], ids=["", "paged"])
+@pytest.mark.parametrize("dtype,tokens,batch,lengths", [
+    (S.F32, 1, 70, None),              # one row each; a second launch of six contexts
+    (S.BF16, 3, 67, None),
+    (S.F32, 40, 9, [0, 1, 0, 40, 5, 0, 31, 33, 0]),   # empty ones first, between and last
+    (S.BF16, 9, 66, [0] * 64 + [9, 2]),               # a launch without rows, then one with
+])
+def test_general_kernel_contexts_share_tiles(dtype, tokens, batch, lengths, paged):
+    """Tiles that hold the rows of several contexts, whole or in part."""
+    T = G.torch()
+    spec = S.Spec(312, "shared-tiles", S.ModelShape(4, 2, 40, 1.0e4), S.ModelShape(3, 3, 24, 5.0e5),
+                  1, (3, 0, 2), dtype, tokens, batch=batch, bias_std=0.2,
+                  span_lo=1 if lengths else 0, span_hi=2 if lengths else 0)
+    prob = S.make_problem(spec)
+    if lengths:
+        rng = np.random.default_rng(7)
+        n = rng.integers(0, 4, size=sum(lengths))
+        prob = dataclasses.replace(
+            prob, tgt_tokens=np.array(lengths, dtype=np.int32),
+            row_ptr=np.concatenate([[0], np.cumsum(n)]).astype(np.int32),
+            col_idx=rng.integers(0, tokens, size=int(n.sum())).astype(np.int32),
+            weight=rng.uniform(-1.0, 1.0, size=int(n.sum())).astype(np.float32))
+    cap = int(prob.tgt_tokens.max())
+    dev = G.DevProblem(prob, cap=cap)
+    assert dev.tr.info().kernel == 0
+    print(f"[general] {tokens} x {batch} paged {paged}", flush=True)
+    (G.run_paged if paged else G.DevProblem.run)(dev)
+    T.cuda.synchronize()
+    rk, rv = O.translate(prob, cap=cap)
+    G.check_full(dev, rk, rv, "shared tiles", ulp_bound=0.6)
+    gk = G.dev_to_f64(dev.tgt_k, spec.dtype)
+    for b, t in enumerate(prob.tgt_tokens):
+        assert np.isnan(gk[:, b, :, int(t):]).all(), "row past the context's end was written"
+    dev.close()
+
+
 @pytest.mark.parametrize("dtype,prec", [(S.F32, kvx.KVX_PREC_BF16X2), (S.BF16, kvx.KVX_PREC_BF16X2),
                                         (S.BF16, kvx.KVX_PREC_F16)])
 def test_plan_weights_by_memory_kind(dtype, prec):
@@ -72,6 +111,7 @@ def test_plan_weights_by_memory_kind(dtype, prec):
     T.cuda.synchronize()
     assert T.equal(dev.tgt_k, want_k) and T.equal(dev.tgt_v, want_v)
     nbytes = host[0].numel() * host[0].element_size()
+    T.cuda.empty_cache()
     block = T.empty(64 << 20, dtype=T.uint8, device="cuda")   # an allocation of its own
     end = block.data_ptr() + block.numel()
     for bad_k, bad_v in ((host[0], dev.w_v), (dev.w_k, host[1]), (dev.w_k, end - nbytes + 16)):

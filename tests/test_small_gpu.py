@@ -52,20 +52,7 @@ def test_small_and_persistent_kernels(case, paged):
         assert (wgs <= 2 * n_cu) == (batch == small), (wgs, n_cu)
         print(f"[small] {case} batch {batch} paged {paged}", flush=True)
         if paged:
-            bs = 16
-            per = -(-cap // bs)
-            table = np.random.default_rng(1).permutation(batch * per).astype(np.int32).reshape(batch, per)
-            pk = T.full((lt, batch * per, ht, bs, dt), float("nan"), dtype=T.bfloat16, device="cuda")
-            pv = T.full_like(pk, float("nan"))
-            ident = prob.row_ptr is None
-            dev.tr(dev.src_k, dev.src_v, pk, pv, cap, None if ident else prob.tgt_tokens,
-                   dev.row_ptr, dev.col_idx, dev.weight, block_table=T.from_numpy(table).cuda(),
-                   block_size=bs)
-            T.cuda.synchronize()
-            idx = T.from_numpy(table.reshape(-1).astype(np.int64)).cuda()
-            for pages, out in ((pk, dev.tgt_k), (pv, dev.tgt_v)):
-                rows = pages[:, idx].view(lt, batch, per, ht, bs, dt).permute(0, 1, 3, 2, 4, 5)
-                out.copy_(rows.reshape(lt, batch, ht, per * bs, dt)[:, :, :, :cap])
+            G.run_paged(dev)
         else:
             dev.run()
         T.cuda.synchronize()
