@@ -55,7 +55,8 @@ struct TiledArgs {
   Strides ss;
   T* tgt[2];                // target K, V
   Strides ts;
-  const T* w[2];            // packed [Lt][npb][nch * kGQ][2][64 lanes][4] (pack_tiled)
+  const T* w[2];            // packed [Lt][npb][nch * kGQ][2][64 lanes][4] (pack_tiled);
+                            // row kernel: [Lt][dout][din], nn.Linear order
   const float* bias[2];     // [Lt][dout] (zeros when the translator has none)
   const int32_t* layer_map; // [Lt][mix]
   int32_t mix, hs, ds, ht, dt, din, dout;

@@ -17,6 +17,7 @@
 #include "kernel_mfma.h"
 #include "fused_launch.h"
 #include "kernel_tiled.h"
+#include "kernel_rows.h"
 #include "staged.h"
 
 using namespace kvx;
@@ -62,6 +63,7 @@ struct kvx_plan {
   double* ft = nullptr;          // [Dt/2]
   void* w[2] = {nullptr, nullptr};  // packed fragments (pack_tiled; fused kernel: fused_feature_of_slot)
   void* wh[2] = {nullptr, nullptr}; // fused, precision F16: packed fp16 fragments
+  void* wr[2] = {nullptr, nullptr}; // small products: nn.Linear order, for the row kernel
   float* bias[2] = {nullptr, nullptr};
   // fused kernel: a zero area that lanes without data load from, and an area
   // that lanes without a valid output row store to (never read), so that
@@ -190,6 +192,20 @@ __global__ void __launch_bounds__(256) pack_fused(const uint16_t* w, uint16_t* o
       }
     }
   }
+}
+
+// The row kernel takes products W [dout][din] of at most so many values.
+// Measured in us per call of 4 layers (row, general kernel): fp32 [24 -> 40]
+// 1024 tokens 9.8, 12.1, 32768 tokens 55, 127; [48 -> 48] 9.6, 11.8 and 145,
+// 118; [64 -> 64] 20, 11.7.  bf16 [32 -> 96] 1024 tokens 9.6, 15.4, 32768 tokens
+// 109, 166; [80 -> 80] 12.6, 15.3 and 183, 166; [80 -> 128] 17.0, 15.2.  At 8
+// source pairs or fewer the general kernel runs 8 times the products: fp32 [16
+// -> 80] 32768 tokens 92, 156; bf16 [16 -> 512] 285, 470, 64 tokens 16.1, 12.8.
+bool rows_product(const kvx_plan& p, bool few_rows) {
+  const int64_t n = int64_t(p.din) * p.dout;
+  if (few_rows) return n <= (p.dtype == KVX_F32 ? 2304 : 6400);
+  const bool narrow = p.din <= 16;
+  return p.dtype == KVX_F32 ? n < 1024 || (narrow && n <= 1280) : n <= 3072 || (narrow && n <= 8192);
 }
 
 // Launch on the default stream with the launch's own status (the runtime's
@@ -324,7 +340,10 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   const size_t smb = want_mask ? size_t(lt) * 2 * nch : 0;
   size_t off_sink = off_ft + align256(ftb);
   size_t off_sm = off_sink + 2 * kSinkBytes;
-  size_t total = off_sm + align256(smb);
+  const bool want_rows = p->kernel == kTiled && (rows_product(*p, true) || rows_product(*p, false));
+  const size_t rbytes = want_rows ? size_t(lt) * dout64 * din64 * esz : 0;
+  size_t off_r0 = off_sm + align256(smb), off_r1 = off_r0 + align256(rbytes);
+  size_t total = off_r1 + align256(rbytes);
   e = hipMalloc(&p->block, total);
   if (e != hipSuccess) return fail(hip_fail(e));
   p->bytes = static_cast<int64_t>(total);
@@ -334,6 +353,10 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   if (want_f16) {
     p->wh[0] = base + off_h0;
     p->wh[1] = base + off_h1;
+  }
+  if (want_rows) {
+    p->wr[0] = base + off_r0;
+    p->wr[1] = base + off_r1;
   }
   p->bias[0] = reinterpret_cast<float*>(base + off_b0);
   p->bias[1] = reinterpret_cast<float*>(base + off_b1);
@@ -361,6 +384,10 @@ kvx_status kvx_plan_create(const kvx_plan_desc* d, kvx_plan** out) {
   } staged;
   for (int kv = 0; kv < 2; ++kv) {
     e = local_weights(wsrc[kv], size_t(lt) * dout64 * din64 * esz, p->device, &wsrc[kv], &staged.p[kv]);
+    if (e != hipSuccess) return fail(hip_fail(e));
+  }
+  for (int kv = 0; kv < 2 && want_rows; ++kv) {
+    e = hipMemcpy(p->wr[kv], wsrc[kv], rbytes, hipMemcpyDeviceToDevice);
     if (e != hipSuccess) return fail(hip_fail(e));
   }
   const dim3 pgrid(static_cast<unsigned>(std::min<size_t>(8192, (size_t(lt) * pelems / 4 + 255) / 256)));
@@ -478,8 +505,16 @@ void launch_small(bool identity, int precision, int grid, hipStream_t st, const 
 // spans 336: 64, 118; 672: 113, 120.
 bool small_call(const kvx_plan* p, int64_t workgroups) { return workgroups <= 2 * p->n_cu; }
 
-// How the general kernel tiles a call's rows: per context or as one list.
-enum TiledKind { kPerContext, kShared };
+// How the general path takes a call: the general kernel with the rows tiled per
+// context or as one list of all contexts' rows, or the row kernel.
+enum TiledKind { kPerContext, kShared, kRows };
+
+// Few rows: the row kernel's workgroups (16 rows of a layer's K or V) run at
+// once, two on a compute unit.
+bool rows_call(const kvx_plan* p, int64_t rows) {
+  if (!p->wr[0] || rows / rows_per_group(p->din) + kMaxBatch >= 1 << 24) return false;  // grid extent
+  return rows_product(*p, rows * p->tgt.n_layers * 2 <= 32 * p->n_cu);
+}
 
 // One list while it saves an eighth of the tiles.  Measured in us per call
 // (list, per context), 28 layers [512 -> 256] fp32 and 24 layers [640 -> 320]
@@ -490,7 +525,7 @@ bool tiles_shared(int64_t context_tiles, int64_t rows) {
   return (rows + kGRows - 1) / kGRows * 8 <= context_tiles * 7;
 }
 
-// The general kernel for one group of contexts.
+// The general path for one group of contexts.
 template <typename T>
 void launch_tiled(const kvx_plan* p, const Strides& ss, const Strides& ts, const char* sk,
                   const char* sv, char* tk, char* tv, const kvx_io& io, bool identity,
@@ -526,6 +561,11 @@ void launch_tiled(const kvx_plan* p, const Strides& ss, const Strides& ts, const
   a.nch = tiled_nch(p->din);
   a.pg = pg;
   a.ba = ba;
+  if (kind == kRows) {
+    for (int kv = 0; kv < 2; ++kv) a.w[kv] = static_cast<const T*>(p->wr[kv]);
+    rows_kernel<T><<<dim3(tiles, p->tgt.n_layers, 2), dim3(256), rows_lds_bytes(p->din), st>>>(a);
+    return;
+  }
   // Four pair blocks per workgroup share one gather of its rows; one each
   // (the four waves then split the contraction) while the larger groups would
   // leave compute units idle.
@@ -733,11 +773,14 @@ extern "C" kvx_status kvx_translate(const kvx_plan* p, const kvx_io* io_in, void
     }
     if (fused)
       small = small_call(p, rt * n_tiles * 2 * Lt);
+    else if (rows_call(p, nr))
+      kind = kRows;
     else if (tiles_shared(rt, nr))
       kind = kShared;
     // a list of all rows has the contexts' first rows in the place of their first tiles
     const int rows_per_tile = small             ? kSRows
                               : fused           ? kMT
+                              : kind == kRows   ? rows_per_group(p->din)
                               : kind == kShared ? 1
                                                 : kGRows;
     int tiles = 0;

@@ -29,8 +29,25 @@ CASES = [
     ((1, 10), (1, 18), 3, 65, 1, 4, S.BF16),
 ]
 
+# products that the row kernel takes, whatever the rows or for few (fp32: under
+# 1024 values, or 2304; bf16: 3072, 6400, or 8192 at 8 source pairs), and the
+# first one past each
+ROW_CASES = [
+    ((1, 2), (1, 2), 1, 17, 2, 0, S.F32),
+    ((1, 22), (1, 46), 1, 2100, 1, 2, S.F32),     # 1012: whatever the rows
+    ((1, 32), (1, 32), 1, 2100, 1, 0, S.F32),     # 1024: not for many rows
+    ((1, 48), (2, 24), 1, 1024, 1, 3, S.F32),     # 2304
+    ((1, 48), (1, 50), 1, 33, 1, 0, S.F32),
+    ((1, 16), (2, 40), 1, 2100, 1, 0, S.F32),     # 1280 of 8 source pairs
+    ((2, 16), (3, 32), 1, 2100, 1, 2, S.BF16),    # 3072
+    ((1, 80), (1, 80), 1, 1024, 1, 0, S.BF16),    # 6400
+    ((1, 80), (1, 82), 1, 1024, 1, 2, S.BF16),
+    ((1, 16), (4, 128), 1, 1100, 2, 0, S.BF16),   # 8192 of 8 source pairs
+    ((3, 8), (1, 10), 2, 5, 66, 2, S.BF16),       # short contexts, two launches
+]
 
-@pytest.mark.parametrize("case", CASES, ids=lambda c: f"{c[0]}-{c[1]}-x{c[2]}-{c[3]}-{c[6]}")
+
+@pytest.mark.parametrize("case", CASES + ROW_CASES, ids=lambda c: f"{c[0]}-{c[1]}-x{c[2]}-{c[3]}-{c[6]}")
 def test_general_kernel_tile_edges(case):
     (hs, ds), (ht, dt), mix, tokens, batch, span, dtype = case
     lt = 4
