@@ -124,11 +124,12 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
     if (threadIdx.x < kGRows) rowi[threadIdx.x] = list_row(a.ba, rt * kGRows + threadIdx.x);
     __syncthreads();
   }
-  // context and position of row r of the tile (position -1: none)
+  // context and position of row r of the tile, and whether there is such a row
   auto row_at = [&](int r) __attribute__((always_inline)) -> int2 {
     if constexpr (SHARE) return rowi[r];
-    return make_int2(b, t0 + r < tt ? t0 + r : -1);
+    return make_int2(b, t0 + r);
   };
+  auto is_row = [&](int t) __attribute__((always_inline)) { return SHARE ? t >= 0 : t < tt; };
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int hd = a.ds / 2;
@@ -147,10 +148,10 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
     const int c = SHARE ? __builtin_amdgcn_readfirstlane(ri.x) : b;
     if constexpr (SHARE) ctx[i] = c;
     e0[i] = 0;
-    e1[i] = t >= 0 ? 1 : 0;
+    e1[i] = is_row(t) ? 1 : 0;
     k0[i] = t;
     w0[i] = 1.f;
-    if (!a.identity && t >= 0) {
+    if (!a.identity && is_row(t)) {
       e0[i] = a.row_ptr[a.ba.row_base[c] + t];
       e1[i] = a.row_ptr[a.ba.row_base[c] + t + 1];
       if (e1[i] > e0[i]) {
@@ -306,7 +307,7 @@ __global__ void __launch_bounds__(256, 4) tiled_kernel(TiledArgs<T> a) {
   for (int v = 0; v < 16; ++v) {
     const int2 ri = row_at(8 * (v / 4) + 4 * (lane / 32) + v % 4);
     const int t = ri.y;
-    if (t < 0) continue;
+    if (!is_row(t)) continue;
     float u0 = acc0[v] + b0, u1 = acc1[v] + b1;
     if (kv == 0) {
       float cs, sn;
