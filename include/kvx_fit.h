@@ -79,7 +79,10 @@ kvx_status kvx_fit_create(const kvx_fit_desc* desc, kvx_fit** out);
  * `stream`; buffers are borrowed until the stream work completes).  Host
  * arguments are validated before anything is enqueued; CSR contents are
  * trusted.  May grow the fit's device scratch (hipMalloc), so it is not for
- * graph capture.  batch == 0 or zero rows is a no-op. */
+ * graph capture: the prepared operands of as many target layers as fit 4 GiB
+ * (1 GiB on a device without room for that; one layer's where that is more),
+ * kept until kvx_fit_destroy or a solve that needs the memory.  batch == 0 or
+ * zero rows is a no-op. */
 kvx_status kvx_fit_accumulate(kvx_fit* fit, const kvx_fit_io* io, void* stream);
 
 /* Solve every (layer, K|V) system with ridge `lambda` >= 0 and write device
@@ -88,8 +91,14 @@ kvx_status kvx_fit_accumulate(kvx_fit* fit, const kvx_fit_io* io, void* stream);
  * b_v [Lt][Ht*Dt] (zeros when fit_bias == 0; may be NULL then).  The
  * accumulators are kept, so more batches may follow.  KVX_EDATA if a system
  * is not positive definite (too few rows for lambda == 0, or lambda < 0);
- * the outputs are then unspecified.  Synchronises `stream` (it reads a
- * device status flag back). */
+ * the outputs are then unspecified.  Its fp64 matrices are allocated by the
+ * first solve and kept; a device without room for them beside the scratch of
+ * kvx_fit_accumulate gets that scratch released.  Synchronises `stream` (it
+ * reads a device status flag back).
+ *
+ * Fault injection: KVX_FAULT=fit-scratch in the environment makes
+ * kvx_fit_accumulate, KVX_FAULT=fit-solve kvx_fit_solve treat its first
+ * allocation as refused for want of memory. */
 kvx_status kvx_fit_solve(kvx_fit* fit, double lambda, float* w_k, float* w_v, float* b_k,
                          float* b_v, void* stream);
 

@@ -907,6 +907,14 @@ kvx_status solve_workspace(void** out) {
   return KVX_OK;
 }
 
+// hipMalloc, or, with KVX_FAULT=`fault` in the environment, the report of a
+// device without room (with nothing allocated), so that what follows it can be
+// tested.
+hipError_t fit_malloc(void** p, size_t bytes, const char* fault) {
+  const char* f = std::getenv("KVX_FAULT");
+  return f && std::strcmp(f, fault) == 0 ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+}
+
 bool valid_side(const kvx_model& m) {
   return m.n_layers > 0 && m.n_kv_heads > 0 && m.head_dim > 0 && std::isfinite(m.rope_base);
 }
@@ -1109,7 +1117,7 @@ kvx_status kvx_fit_accumulate(kvx_fit* f, const kvx_fit_io* io_in, void* stream)
         f->prep = nullptr;
         f->prep_bytes = 0;
       }
-      hipError_t e = hipMalloc(&f->prep, per_layer * lg);
+      hipError_t e = fit_malloc(&f->prep, per_layer * lg, "fit-scratch");
       if (e == hipErrorOutOfMemory && group(30) < lg) {
         (void)hipGetLastError();  // handled: not the next launch's error
         f->prep_shift = 30;
@@ -1240,7 +1248,19 @@ kvx_status kvx_fit_solve(kvx_fit* f, double lambda, float* w_k, float* w_v, floa
       f->solve_buf = nullptr;
       f->solve_bytes = 0;
     }
-    FIT_HIP(hipMalloc(&f->solve_buf, need));
+    hipError_t e = fit_malloc(&f->solve_buf, need, "fit-solve");
+    if (e == hipErrorOutOfMemory && f->prep) {
+      // the prepared operands are scratch of finished accumulations: give
+      // their memory to the solve (the next accumulation allocates anew)
+      (void)hipGetLastError();  // handled: not the next launch's error
+      FIT_HIP(hipStreamSynchronize(st));
+      FIT_HIP(hipFree(f->prep));
+      f->prep = nullptr;
+      f->prep_bytes = 0;
+      e = hipMalloc(&f->solve_buf, need);
+    }
+    if (e != hipSuccess) f->solve_buf = nullptr;
+    FIT_HIP(e);
     f->solve_bytes = need;
   }
   char* base = static_cast<char*>(f->solve_buf);

@@ -4,6 +4,8 @@ and enqueues nothing, so the target cache keeps its previous contents; the
 next call without the variable runs normally.  This is the path a runtime
 takes to its fallback (native prefill) when a translation is unavailable.
 No kernel is made to fail: the library returns before any launch.
+Likewise the allocations of a fit (KVX_FAULT=fit-scratch, fit-solve) are
+treated as refused without being tried.
 """
 import os
 
@@ -92,6 +94,74 @@ def test_injected_launch_fault_staged(fault_env):
     U.check_full(dev, rk, rv, "staged after fault", 0.75)
     del keep
     dev.close()
+
+
+def _fit(layers, tokens, batch):
+    """A fit of `layers` layers [512 -> 256] without bias (whose sums are
+    atomic), and its drawn caches."""
+    T = U.torch()
+    g = T.Generator(device="cuda").manual_seed(5)
+    draw = lambda *s: T.randn(s, generator=g, device="cuda").bfloat16()
+    src, tgt = S.ModelShape(3, 4, 128, 1.0e6), S.ModelShape(layers, 2, 128, 1.0e6)
+    x = [draw(3, batch, 4, tokens, 128) for _ in range(2)]
+    y = [draw(layers, batch, 2, tokens, 128) for _ in range(2)]
+    fit = kvx.Fitter(src, tgt, 1, [l % 3 for l in range(layers)], kvx.KVX_BF16, fit_bias=False)
+    return fit, (x[0], x[1], y[0], y[1])
+
+
+def test_fit_scratch_without_room_for_it(fault_env):
+    """A device without room for a fit's scratch gets smaller groups of
+    layers: 28 layers of 16384 rows in three of 1 GiB at most, to the same
+    bits.  The limit stays with the fit."""
+    fit, caches = _fit(28, 4096, 4)
+    print("[fault] KVX_FAULT=fit-scratch", flush=True)
+    fit.accumulate(*caches)
+    want = fit.solve(1.0)
+    fit.close()
+    fit, caches = _fit(28, 4096, 4)
+    held = fit.info().device_bytes
+    os.environ["KVX_FAULT"] = "fit-scratch"
+    fit.accumulate(*caches)
+    del os.environ["KVX_FAULT"]
+    assert 0 < fit.info().device_bytes - held <= 1 << 30
+    fit.accumulate(*caches)
+    assert fit.info().device_bytes - held <= 1 << 30
+    fit.reset()
+    fit.accumulate(*caches)
+    for a, b in zip(fit.solve(1.0), want):
+        assert U.torch().equal(a, b)
+    fit.close()
+
+
+def test_fit_solve_takes_the_scratch(fault_env):
+    """A solve without room for its matrices releases the scratch of the
+    accumulations and goes on; a fit without scratch reports KVX_ENOMEM, and
+    works once there is room."""
+    fit, caches = _fit(3, 200, 1)
+    print("[fault] KVX_FAULT=fit-solve", flush=True)
+    empty = fit.info().device_bytes
+    os.environ["KVX_FAULT"] = "fit-solve"
+    with pytest.raises(kvx.KvxError) as err:
+        fit.solve(1.0)
+    assert err.value.status == kvx.KVX_ENOMEM
+    del os.environ["KVX_FAULT"]
+    fit.accumulate(*caches)
+    want = fit.solve(1.0)
+    fit.close()
+    fit, caches = _fit(3, 200, 1)
+    fit.accumulate(*caches)
+    assert fit.info().device_bytes > empty
+    os.environ["KVX_FAULT"] = "fit-solve"
+    got = fit.solve(1.0)
+    del os.environ["KVX_FAULT"]
+    solve_bytes = 6 * (512 * 512 + 512 * 256) * 8 + 256
+    assert fit.info().device_bytes == empty + solve_bytes, "the scratch was kept"
+    fit.accumulate(*caches)        # allocates its scratch again
+    again = fit.solve(2.0)         # twice the rows, twice the ridge: the same weights
+    for a, b, c in zip(got, want, again):
+        assert U.torch().equal(a, b)
+        U.torch().testing.assert_close(c, b, rtol=1e-4, atol=1e-5)
+    fit.close()
 
 
 def test_a_failed_plan_leaves_the_next_calls_alone():
