@@ -306,6 +306,23 @@ __device__ __forceinline__ uint4 pack8_f16(const float* z) {
   return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
+// The arithmetic of the operands, with its roundings stated: left to the
+// compiler, which of the products become fused multiply-adds differs from one
+// copy of the transform to the next, and with it a row's last bits between the
+// places in a call that it may take.
+
+// De-rotation of a pair by the angle of cos c, sin s.
+__device__ __forceinline__ void unrope(float x0, float x1, float c, float s, float& y0, float& y1) {
+#pragma clang fp contract(off)
+  y0 = __builtin_fmaf(x0, c, x1 * s);
+  y1 = __builtin_fmaf(x1, c, -(x0 * s));
+}
+// w0 x + w1 y
+__device__ __forceinline__ float pool2(float w0, float x, float w1, float y) {
+#pragma clang fp contract(off)
+  return __builtin_fmaf(w0, x, w1 * y);
+}
+
 // Operand precision of computed operands (de-rotated K, pooled V).
 enum Prec { kBF16X2 = 0, kBF16 = 1, kF16 = 2 };
 
@@ -774,18 +791,18 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
               } else {
                 rope_cs(f[i], d, cd, sd);
               }
-              const float y0 = w0 * x0[i] + w1 * (v0[i] * cd + v1[i] * sd);
-              const float y1 = w0 * x1[i] + w1 * (v1[i] * cd - v0[i] * sd);
-              float cs_, sn;
+              float y0, y1, cs_, sn;
+              unrope(v0[i], v1[i], cd, sd, y0, y1);
+              y0 = pool2(w0, x0[i], w1, y0);
+              y1 = pool2(w0, x1[i], w1, y1);
               rope_cs(f[i], k0, cs_, sn);
-              z0[i] = y0 * cs_ + y1 * sn;
-              z1[i] = y1 * cs_ - y0 * sn;
+              unrope(y0, y1, cs_, sn, z0[i], z1[i]);
             }
           } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-              z0[i] = w0 * x0[i] + w1 * v0[i];
-              z1[i] = w0 * x1[i] + w1 * v1[i];
+              z0[i] = pool2(w0, x0[i], w1, v0[i]);
+              z1[i] = pool2(w0, x1[i], w1, v1[i]);
             }
           }
         } else {
@@ -804,8 +821,7 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
               } else {
                 rope_cs(f[i], k, cs_, sn);
               }
-              y0 = x0[i] * cs_ + x1[i] * sn;
-              y1 = x1[i] * cs_ - x0[i] * sn;
+              unrope(x0[i], x1[i], cs_, sn, y0, y1);
             }
             z0[i] = y0;
             z1[i] = y1;
@@ -826,11 +842,10 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
               if (is_k) {
                 float cs_, sn;
                 rope_cs(f[i], k, cs_, sn);
-                y0 = x0[i] * cs_ + x1[i] * sn;
-                y1 = x1[i] * cs_ - x0[i] * sn;
+                unrope(x0[i], x1[i], cs_, sn, y0, y1);
               }
-              z0[i] += w * y0;
-              z1[i] += w * y1;
+              z0[i] = __builtin_fmaf(w, y0, z0[i]);
+              z1[i] = __builtin_fmaf(w, y1, z1[i]);
             }
           }
         }
@@ -1042,8 +1057,10 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
           rel(d1);
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
-            z0[i] = w0 * x0[i] + w1 * (v0[i] * cd[i] + v1[i] * sd[i]);
-            z1[i] = w0 * x1[i] + w1 * (v1[i] * cd[i] - v0[i] * sd[i]);
+            float y0, y1;
+            unrope(v0[i], v1[i], cd[i], sd[i], y0, y1);
+            z0[i] = pool2(w0, x0[i], w1, y0);
+            z1[i] = pool2(w0, x1[i], w1, y1);
           }
           if (any3) {
             rel(d2);
@@ -1051,8 +1068,10 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
             unpack8(y[1], v1);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-              z0[i] += w2 * (v0[i] * cd[i] + v1[i] * sd[i]);
-              z1[i] += w2 * (v1[i] * cd[i] - v0[i] * sd[i]);
+              float y0, y1;
+              unrope(v0[i], v1[i], cd[i], sd[i], y0, y1);
+              z0[i] = __builtin_fmaf(w2, y0, z0[i]);
+              z1[i] = __builtin_fmaf(w2, y1, z1[i]);
             }
           }
           for (int e = r0.x + 3; e < r0.x + n; ++e) {
@@ -1062,33 +1081,32 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
             unpack8(ld_src<STREAM>(gp + k * a.ss.t + half), v1);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-              float c, sn;
+              float c, sn, y0, y1;
               rope_cs(fsl[i0 + i], k - k0, c, sn);
-              z0[i] += w * (v0[i] * c + v1[i] * sn);
-              z1[i] += w * (v1[i] * c - v0[i] * sn);
+              unrope(v0[i], v1[i], c, sn, y0, y1);
+              z0[i] = __builtin_fmaf(w, y0, z0[i]);
+              z1[i] = __builtin_fmaf(w, y1, z1[i]);
             }
           }
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
             float c, sn;
             rope_cs(fsl[i0 + i], k0, c, sn);
-            const float y0 = z0[i], y1 = z1[i];
-            z0[i] = y0 * c + y1 * sn;
-            z1[i] = y1 * c - y0 * sn;
+            unrope(z0[i], z1[i], c, sn, z0[i], z1[i]);
           }
         } else {
 #pragma unroll
           for (int i = 0; i < 8; ++i) {
-            z0[i] = w0 * x0[i] + w1 * v0[i];
-            z1[i] = w0 * x1[i] + w1 * v1[i];
+            z0[i] = pool2(w0, x0[i], w1, v0[i]);
+            z1[i] = pool2(w0, x1[i], w1, v1[i]);
           }
           if (any3) {
             unpack8(y[0], v0);
             unpack8(y[1], v1);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-              z0[i] += w2 * v0[i];
-              z1[i] += w2 * v1[i];
+              z0[i] = __builtin_fmaf(w2, v0[i], z0[i]);
+              z1[i] = __builtin_fmaf(w2, v1[i], z1[i]);
             }
           }
           for (int e = r0.x + 3; e < r0.x + n; ++e) {
@@ -1098,8 +1116,8 @@ __global__ void __launch_bounds__(kThreads) fused_kernel(FusedArgs a) {
             unpack8(ld_src<STREAM>(gp + k * a.ss.t + half), v1);
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-              z0[i] += w * v0[i];
-              z1[i] += w * v1[i];
+              z0[i] = __builtin_fmaf(w, v0[i], z0[i]);
+              z1[i] = __builtin_fmaf(w, v1[i], z1[i]);
             }
           }
         }

@@ -11,8 +11,10 @@
 // dependent loads (alignment, source rows, later weights) and the launch.
 //
 // Operands, chunks, pair blocks and packed weights are those of the
-// persistent kernel, so are the split and the order of the sums; the product
-// is taken as U = Z W^T, so a lane holds one output feature pair of 16 tokens.
+// persistent kernel, so are the pooling, the angles, the split and the order of
+// the sums: a row's bits do not depend on the size of the call it came in.  The
+// product is taken as U = Z W^T, so a lane holds one output feature pair of 16
+// tokens.
 // Measured per call, the persistent kernel's time in brackets: 28 layers
 // [512 -> 256], 16 tokens 11.4 us [21.9], 128 tokens 14.1 us [22.2]; 28 layers
 // [3072 -> 512], spans of 1-2, 128 tokens 64 us [118].
@@ -24,6 +26,22 @@ namespace kvx {
 
 constexpr int kSRows = 32;  // target rows per workgroup: one matrix instruction's
 constexpr int kSRing = 8;   // k-steps of weights in flight per wave (16: no faster, spills)
+
+// The output's rotation, with the roundings of the persistent kernel's epilogue.
+
+// Rotation of a pair by the angle of cos c, sin s.
+__device__ __forceinline__ void rope(float x0, float x1, float c, float s, float& y0, float& y1) {
+#pragma clang fp contract(off)
+  y0 = __builtin_fmaf(x0, c, -(x1 * s));
+  y1 = __builtin_fmaf(x0, s, x1 * c);
+}
+// cos c, sin s of an angle advanced by that of cos cd, sin sd.
+__device__ __forceinline__ void advance_cs(float cd, float sd, float& c, float& s) {
+#pragma clang fp contract(off)
+  const float c2 = __builtin_fmaf(c, cd, -(s * sd));
+  s = __builtin_fmaf(s, cd, c * sd);
+  c = c2;
+}
 
 template <bool IDENT, int PREC>
 __global__ void __launch_bounds__(256, 2) small_kernel(FusedArgs a) {
@@ -144,45 +162,59 @@ __global__ void __launch_bounds__(256, 2) small_kernel(FusedArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
         rope_cs(fsl[i0 + i], k0, ca[i], sa[i]);
-        if constexpr (!IDENT) rope_cs(fsl[i0 + i], k1, cb[i], sb[i]);
+        if constexpr (!IDENT) rope_cs(fsl[i0 + i], n > 1 ? k1 - k0 : 0, cb[i], sb[i]);
       }
     }
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const float c0 = is_k ? ca[i] : 1.f, s0 = is_k ? sa[i] : 0.f;
-      z0[i] = is_k ? x0[i] * c0 + x1[i] * s0 : x0[i];
-      z1[i] = is_k ? x1[i] * c0 - x0[i] * s0 : x1[i];
-    }
+    // the persistent kernel's resident order, where it would take the call, adds
+    // a K row's later entries in the first one's frame, the others to the
+    // rotated sum
+    const bool frame = !IDENT && a.interleave == 2;
     if constexpr (!IDENT) {
-      auto add = [&](const uint4 p, const uint4 q, float we, const float* cs,
-                     const float* sn) KVX_INLINE {
-        float v0[8], v1[8];
-        unpack8(p, v0);
-        unpack8(q, v1);
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          z0[i] += we * (is_k ? v0[i] * cs[i] + v1[i] * sn[i] : v0[i]);
-          z1[i] += we * (is_k ? v1[i] * cs[i] - v0[i] * sn[i] : v1[i]);
-        }
-      };
+      // the first two entries, K in the first one's frame
+      float v0[8], v1[8];
+      unpack8(y[c][0], v0);
+      unpack8(y[c][1], v1);
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        z0[i] *= w0;
-        z1[i] *= w0;
+        if (is_k) unrope(v0[i], v1[i], cb[i], sb[i], v0[i], v1[i]);
+        z0[i] = pool2(w0, x0[i], w1, v0[i]);
+        z1[i] = pool2(w0, x1[i], w1, v1[i]);
       }
-      add(y[c][0], y[c][1], w1, cb, sb);
-      for (int e = e0 + 2; e < e0 + n; ++e) {
-        const int k = a.col_idx[e];
-        const bf16_t* p = gp + k * a.ss.t;
-        float cs[8], sn[8];
-        if (is_k) {
+    } else {
 #pragma unroll
-          for (int i = 0; i < 8; ++i) rope_cs(fsl[i0 + i], k, cs[i], sn[i]);
-        }
-        add(*reinterpret_cast<const uint4*>(p), *reinterpret_cast<const uint4*>(p + half),
-            a.weight[e], cs, sn);
+      for (int i = 0; i < 8; ++i) {
+        z0[i] = x0[i];
+        z1[i] = x1[i];
       }
     }
+    auto rotate = [&]() KVX_INLINE {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) unrope(z0[i], z1[i], ca[i], sa[i], z0[i], z1[i]);
+    };
+    if (is_k && !frame) rotate();
+    if constexpr (!IDENT) {
+      for (int e = e0 + 2; e < e0 + n; ++e) {
+        const int k = a.col_idx[e];
+        const float we = a.weight[e];
+        const bf16_t* p = gp + k * a.ss.t;
+        const uint4 q0 = *reinterpret_cast<const uint4*>(p);
+        const uint4 q1 = *reinterpret_cast<const uint4*>(p + half);
+        float v0[8], v1[8], cs[8], sn[8];
+        if (is_k) {  // while the entry's rows arrive
+#pragma unroll
+          for (int i = 0; i < 8; ++i) rope_cs(fsl[i0 + i], frame ? k - k0 : k, cs[i], sn[i]);
+        }
+        unpack8(q0, v0);
+        unpack8(q1, v1);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          if (is_k) unrope(v0[i], v1[i], cs[i], sn[i], v0[i], v1[i]);
+          z0[i] = __builtin_fmaf(we, v0[i], z0[i]);
+          z1[i] = __builtin_fmaf(we, v1[i], z1[i]);
+        }
+      }
+    }
+    if (is_k && frame) rotate();
     if (PREC == kF16) {
       *reinterpret_cast<uint4*>(hi) = pack8_f16(z0);
       *reinterpret_cast<uint4*>(hi + 64) = pack8_f16(z1);
@@ -237,8 +269,13 @@ __global__ void __launch_bounds__(256, 2) small_kernel(FusedArgs a) {
     if (more) lds_barrier();
   }
 
-  // bias, target rotation, bf16; a half-wave stores 32 features of a row
+  // bias, target rotation, bf16; a half-wave stores 32 features of a row.  The
+  // angle is the persistent kernel's: formed for the first 32 rows of its
+  // 128-row tile and advanced by the rotation by 32 positions.
   if (!on) return;
+  float c32 = 1.f, s32 = 0.f;
+  if (is_k) rope_cs(ft, 32, c32, s32);
+  const int ahead = t0 % kMT;  // rows from that tile's first to this one's
   bf16_t* dst = a.tgt[kv] + l * a.ts.l + hp * a.ts.h + fi;
 #pragma unroll
   for (int v = 0; v < 16; ++v) {
@@ -247,10 +284,9 @@ __global__ void __launch_bounds__(256, 2) small_kernel(FusedArgs a) {
     float u0 = acc0[v] + b0, u1 = acc1[v] + b1;
     if (is_k) {
       float cs, sn;
-      rope_cs(ft, t, cs, sn);
-      const float y0 = u0 * cs - u1 * sn, y1 = u1 * cs + u0 * sn;
-      u0 = y0;
-      u1 = y1;
+      rope_cs(ft, t - ahead, cs, sn);
+      for (int m = 0; m < ahead; m += kSRows) advance_cs(c32, s32, cs, sn);
+      rope(u0, u1, cs, sn, u0, u1);
     }
     const int32_t blk = a.pg.table ? a.pg.table[b * a.pg.max_blocks + t / a.pg.block_size] : 0;
     bf16_t* q = dst + target_row(a.pg, a.ts, b, t, blk);
