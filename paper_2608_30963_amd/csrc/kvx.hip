@@ -498,12 +498,22 @@ void launch_small(bool identity, int precision, int grid, hipStream_t st, const 
 }
 
 // The small-call kernel while all of its 32-row workgroups run at once, two on
-// a compute unit.  Measured in us per call (small, persistent) by workgroups,
-// on 256 compute units: [512 -> 256] 224: 14.1, 22.2; 448: 17.5, 22.4; 672:
-// 26.8, 22.9.  [256 -> 1024] spans 416: 15.2, 21.6; 624: 22.0, 22.6; 832: 26.7,
-// 24.8.  [256 -> 1024] identity 448: 14.7, 17.1; 896: 24.1, 16.6.  [3072 -> 512]
-// spans 336: 64, 118; 672: 113, 120.
-bool small_call(const kvx_plan* p, int64_t workgroups) { return workgroups <= 2 * p->n_cu; }
+// a compute unit; the second one pays while the operands cost something (spans,
+// split products over several chunks), less where they pass straight through.
+// Measured in us per call (small, persistent kernel), on 256 compute units, with
+// the weights in the caches and after a flush of them, by workgroups.  Spans,
+// 16 layers [512 -> 256] 512: 21, 33 and 37, 51; [128 -> 256] 13.1, 17.2 and
+// 25, 30.  Identity, 28 layers [512 -> 256] split 280: 16.4, 22.7 and 30, 34;
+// 504: 18.5, 23.5 and 32, 34; fp16 392: 14.6, 19.1 and 30.6, 30.6; 448: 15.4,
+// 18.0 and 32.2, 29.1.  16 layers [256 -> 256] split 384: 14.9, 16.2 and 25.6,
+// 26.6; 512: 15.6, 16.6 and 27.0, 27.0; [128 -> 256] 288: 11.6, 14.0 and 21.6,
+// 24.0; 512: 14.0, 13.5 and 24.5, 23.8.
+bool small_call(const kvx_plan* p, bool identity, int64_t workgroups) {
+  const int nch = p->din / 128;
+  const bool split = p->precision == KVX_PREC_BF16X2 || p->precision == KVX_PREC_BF16X2_OUTLIER;
+  const int quarters = !identity ? 8 : nch == 1 ? 5 : split && nch > 2 ? 8 : 6;
+  return workgroups * 4 <= int64_t(quarters) * p->n_cu;
+}
 
 // How the general path takes a call: the general kernel with the rows tiled per
 // context or as one list of all contexts' rows, or the row kernel.
@@ -772,7 +782,7 @@ extern "C" kvx_status kvx_translate(const kvx_plan* p, const kvx_io* io_in, void
       nr += ttok[b0 + i];
     }
     if (fused)
-      small = small_call(p, rt * n_tiles * 2 * Lt);
+      small = small_call(p, identity, rt * n_tiles * 2 * Lt);
     else if (rows_call(p, nr))
       kind = kRows;
     else if (tiles_shared(rt, nr))

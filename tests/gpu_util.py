@@ -15,6 +15,8 @@ checked bit-exact by ``test_probes_gpu.py``.
 """
 from __future__ import annotations
 
+import dataclasses
+
 import numpy as np
 
 from paper_2608_30963_amd import kvx, synth as S
@@ -103,6 +105,27 @@ class DevProblem:
 
     def close(self):
         self.tr.close()
+
+
+def small_kernel(prob: S.Problem, precision, first=0) -> bool:
+    """Whether a bf16 plan's call of ``prob`` runs the small-call kernel (as
+    against the persistent one), by the library's rule on the workgroups of 32
+    rows, for the launch of the 64 contexts from ``first``."""
+    spec = prob.spec
+    n_cu = torch().cuda.get_device_properties(0).multi_processor_count
+    rows = sum(-(-int(t) // 32) for t in prob.tgt_tokens[first:first + 64])
+    wgs = rows * -(-spec.d_out // 256) * 2 * spec.tgt.n_layers
+    split = precision in (kvx.KVX_PREC_BF16X2, kvx.KVX_PREC_BF16X2_OUTLIER)
+    nch = spec.d_in // 128
+    quarters = 8 if prob.row_ptr is not None else 5 if nch == 1 else 8 if split and nch > 2 else 6
+    return 4 * wgs <= quarters * n_cu
+
+
+def more_layers(spec: S.Spec, k: int) -> S.Spec:
+    """``spec`` with its target layers and their layer map repeated k times:
+    the same call, large enough for the persistent kernel."""
+    tgt = dataclasses.replace(spec.tgt, n_layers=k * spec.tgt.n_layers)
+    return dataclasses.replace(spec, tgt=tgt, layer_map=tuple(spec.layer_map) * k)
 
 
 def run_paged(dev: DevProblem, bs: int = 16):

@@ -1,8 +1,8 @@
 """The small-call kernel (32-row tiles, segments of four chunks, two with
 spans) and the persistent kernel on the same shapes, against the oracle and
-against each other, bit for bit.  The call's size alone selects the kernel: at
-most two 32-row workgroups per compute unit run the small one, so the second
-batch size of each case is past that."""
+against each other, bit for bit.  The call's size selects the kernel
+(gpu_util.small_kernel), so the second batch size of each case is past the
+line."""
 import numpy as np
 import pytest
 
@@ -41,7 +41,6 @@ def test_small_and_persistent_kernels(case, paged):
     (hs, ds), (ht, dt), mix, tokens, span, prec, small, large = case
     T = G.torch()
     lt = 5
-    n_cu = T.cuda.get_device_properties(0).multi_processor_count
     for batch in (small, large):
         spec = S.Spec(330, "small", S.ModelShape(4, hs, ds, 1.0e4), S.ModelShape(lt, ht, dt, 5.0e5),
                       mix, tuple((l + j) % 4 for l in range(lt) for j in range(mix)), S.BF16, tokens,
@@ -52,8 +51,7 @@ def test_small_and_persistent_kernels(case, paged):
         cap = int(prob.tgt_tokens.max())
         dev = G.DevProblem(prob, prec, cap=cap, outliers=marks)
         assert dev.tr.info().kernel == 1
-        wgs = sum(-(-int(t) // 32) for t in prob.tgt_tokens) * -(-ht * dt // 256) * 2 * lt
-        assert (wgs <= 2 * n_cu) == (batch == small), (wgs, n_cu)
+        assert G.small_kernel(prob, prec) == (batch == small)
         print(f"[small] {case} batch {batch} paged {paged}", flush=True)
         if paged:
             G.run_paged(dev)
@@ -89,7 +87,7 @@ def test_bits_do_not_depend_on_the_call(case, paged):
     dev = G.DevProblem(prob, prec, cap=cap, outliers=marks)
     n_cu = T.cuda.get_device_properties(0).multi_processor_count
     wgs = [-(-int(t) // 32) * -(-ht * dt // 256) * 2 * lt for t in prob.tgt_tokens]
-    assert max(wgs) <= n_cu and sum(wgs) > 2 * n_cu, (wgs, n_cu)
+    assert max(wgs) <= n_cu and not G.small_kernel(prob, prec), (wgs, n_cu)
     print(f"[small] {case} alone and in a batch, paged {paged}", flush=True)
     (G.run_paged if paged else G.DevProblem.run)(dev)
     first = 0
