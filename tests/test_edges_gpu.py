@@ -26,13 +26,20 @@ def _spec(**kw):
     return S.Spec(**base)
 
 
-def _check(prob, precision=kvx.KVX_PREC_BF16X2, expect_kernel=1, expect_order=None):
+# A call's size selects the small-call kernel or the persistent one: each case
+# runs as it is, and with more target layers.
+KERNELS = pytest.mark.parametrize("kernel", ["small", "persistent"])
+
+
+def _check(prob, precision=kvx.KVX_PREC_BF16X2, expect_kernel=1, expect_order=None, kernel=None):
     print(f"[edges] {prob.spec.name} T={prob.spec.src_tokens} B={prob.spec.batch} "
           f"tt={list(prob.tgt_tokens)[:8]}", flush=True)
     dev = U.DevProblem(prob, precision, cap=max(1, int(prob.tgt_tokens.max())))
     assert dev.tr.info().kernel == expect_kernel
     if expect_order is not None:
         assert dev.tr.info().tile_order == expect_order
+    for first in range(0, prob.spec.batch, 64):
+        assert kernel is None or U.small_kernel(prob, precision, first) == (kernel == "small")
     dev.run()
     U.torch().cuda.synchronize()
     rk, rv = O.translate(prob, cap=dev.cap)
@@ -44,19 +51,28 @@ def _check(prob, precision=kvx.KVX_PREC_BF16X2, expect_kernel=1, expect_order=No
     dev.close()
 
 
-def test_batch_over_one_launch():
+def _sized(spec, kernel, k):
+    return spec if kernel == "small" else U.more_layers(spec, k)
+
+
+@KERNELS
+def test_batch_over_one_launch(kernel):
     """70 contexts: the host splits them into launches of 64 and 6."""
-    _check(S.make_problem(_spec(name="batch70", src_tokens=24, batch=70)))
+    spec = _sized(_spec(name="batch70", src_tokens=24, batch=70), kernel, 17)
+    _check(S.make_problem(spec), kernel=kernel)
 
 
-def test_single_source_token():
-    _check(S.make_problem(_spec(name="one-token", src_tokens=1, batch=3)))
+@KERNELS
+def test_single_source_token(kernel):
+    spec = _sized(_spec(name="one-token", src_tokens=1, batch=3), kernel, 33)
+    _check(S.make_problem(spec), kernel=kernel)
 
 
-def test_empty_contexts_and_rows():
+@KERNELS
+def test_empty_contexts_and_rows(kernel):
     """Hand-made alignment: a context with no target tokens, rows with no
     entries (bias-only output), entries out of order and repeated."""
-    spec = _spec(name="empty-rows", src_tokens=37, batch=3, span_lo=1, span_hi=2)
+    spec = _sized(_spec(name="empty-rows", src_tokens=37, batch=3, span_lo=1, span_hi=2), kernel, 43)
     prob = S.make_problem(spec)
     rng = np.random.default_rng(5)
     tt = np.array([0, 5, 37], dtype=np.int32)
@@ -72,19 +88,20 @@ def test_empty_contexts_and_rows():
     weight = rng.uniform(-1.0, 1.0, size=len(cols)).astype(np.float32)
     prob = dataclasses.replace(prob, tgt_tokens=tt, row_ptr=row_ptr, col_idx=col_idx,
                                weight=weight)
-    _check(prob)
+    _check(prob, kernel=kernel)
 
 
-def test_long_spans():
+@KERNELS
+def test_long_spans(kernel):
     """Rows pooling 3 to 7 source tokens (the fused kernel prefetches the
     second entry, requests the third entry's index early and reads the rest
     in its pooling loop), drawn spans and a hand-made map with entries out
     of order, repeated, and weights of both signs; split and fp16 operand
     precisions."""
-    spec = _spec(name="long-spans", src_tokens=700, batch=2, span_lo=3, span_hi=7)
+    spec = _sized(_spec(name="long-spans", src_tokens=700, batch=2, span_lo=3, span_hi=7), kernel, 16)
     prob = S.make_problem(spec)
-    _check(prob)
-    _check(prob, precision=kvx.KVX_PREC_F16)
+    _check(prob, kernel=kernel)
+    _check(prob, precision=kvx.KVX_PREC_F16, kernel=kernel)
     rng = np.random.default_rng(11)
     tt = np.array([90, 161], dtype=np.int32)
     counts, cols = [], []
@@ -96,19 +113,21 @@ def test_long_spans():
     row_ptr = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     weight = rng.uniform(-1.0, 1.0, size=len(cols)).astype(np.float32)
     _check(dataclasses.replace(prob, tgt_tokens=tt, row_ptr=row_ptr,
-                               col_idx=np.array(cols, dtype=np.int32), weight=weight))
+                               col_idx=np.array(cols, dtype=np.int32), weight=weight), kernel=kernel)
 
 
-def test_two_heads_per_chunk_mix2_partial_tile():
+@KERNELS
+def test_two_heads_per_chunk_mix2_partial_tile(kernel):
     """Ds = 64 (a K-chunk spans two source heads), two mixed source layers,
     and dout = 384 (the second output tile is half used)."""
     spec = _spec(name="ds64-mix2-dout384", src=S.ModelShape(4, 2, 64, 1.0e4),
                  tgt=S.ModelShape(2, 3, 128, 1.0e6), mix=2, layer_map=(0, 1, 3, 2),
                  src_tokens=200, batch=2)
-    _check(S.make_problem(spec))
+    spec = _sized(spec, kernel, 8)
+    _check(S.make_problem(spec), kernel=kernel)
     _check(S.make_problem(dataclasses.replace(spec, name="ds64-mix2-spans", span_lo=1,
-                                              span_hi=2)))
-    _check(S.make_problem(spec), precision=kvx.KVX_PREC_F16)
+                                              span_hi=2)), kernel=kernel)
+    _check(S.make_problem(spec), precision=kvx.KVX_PREC_F16, kernel=kernel)
 
 
 def test_interleaved_tile_order():
@@ -125,15 +144,16 @@ def test_interleaved_tile_order():
     n_cu = U.torch().cuda.get_device_properties(0).multi_processor_count
     units = sum(-(-int(t) // 128) for t in prob.tgt_tokens) * 2 * 4 * 2
     assert units > n_cu, (units, n_cu)
-    _check(prob, expect_order=1)
-    _check(prob, precision=kvx.KVX_PREC_F16, expect_order=1)
+    _check(prob, expect_order=1, kernel="persistent")
+    _check(prob, precision=kvx.KVX_PREC_F16, expect_order=1, kernel="persistent")
     spans = S.make_problem(dataclasses.replace(spec, name="interleaved-spans", batch=4,
                                                span_lo=1, span_hi=3))
-    _check(spans, expect_order=1)
+    _check(spans, expect_order=1, kernel="persistent")
     # a shorter contraction keeps the contiguous order
-    short = S.make_problem(dataclasses.replace(spec, name="contiguous", mix=1,
-                                               layer_map=(0, 1, 2, 3), src_tokens=300))
-    _check(short, expect_order=0)
+    for tokens, kernel in ((300, "small"), (400, "persistent")):
+        short = S.make_problem(dataclasses.replace(spec, name="contiguous", mix=1,
+                                                   layer_map=(0, 1, 2, 3), src_tokens=tokens))
+        _check(short, expect_order=0, kernel=kernel)
 
 
 def test_resident_order_shapes():
@@ -144,8 +164,9 @@ def test_resident_order_shapes():
     one = _spec(name="resident-1chunk", src=S.ModelShape(2, 1, 128, 1.0e6),
                 tgt=S.ModelShape(2, 3, 128, 1.0e4), layer_map=(1, 0), src_tokens=700, batch=3,
                 span_lo=1, span_hi=3)
-    _check(S.make_problem(one), expect_order=2)
-    _check(S.make_problem(one), precision=kvx.KVX_PREC_F16, expect_order=2)
+    for spec, kernel in ((one, "small"), (U.more_layers(one, 3), "persistent")):
+        _check(S.make_problem(spec), expect_order=2, kernel=kernel)
+        _check(S.make_problem(spec), precision=kvx.KVX_PREC_F16, expect_order=2, kernel=kernel)
     two = _spec(name="resident-groups", src=S.ModelShape(3, 2, 128, 1.0e6),
                 tgt=S.ModelShape(2, 6, 128, 1.0e4), layer_map=(2, 0), src_tokens=2000,
                 batch=9, span_lo=1, span_hi=2)
@@ -153,19 +174,25 @@ def test_resident_order_shapes():
     n_cu = U.torch().cuda.get_device_properties(0).multi_processor_count
     groups = sum(-(-int(t) // 128) for t in prob.tgt_tokens) * 2 * 2
     assert groups > n_cu, (groups, n_cu)
-    _check(prob, expect_order=2)
+    _check(prob, expect_order=2, kernel="persistent")
     # identity alignment on such a plan takes the contiguous order
-    _check(S.make_problem(dataclasses.replace(two, name="resident-plan-identity", span_lo=0,
-                                              span_hi=0, batch=2, src_tokens=300)))
+    for tokens, kernel in ((300, "small"), (700, "persistent")):
+        _check(S.make_problem(dataclasses.replace(two, name="resident-plan-identity", span_lo=0,
+                                                  span_hi=0, batch=2, src_tokens=tokens)),
+               kernel=kernel)
 
 
-def test_strided_source_view():
-    """Source K/V are views into larger caches (extra tokens after T_s)."""
+@KERNELS
+def test_strided_source_view(kernel):
+    """Source K/V are views into larger caches (extra tokens after T_s), and
+    the target's rows lie apart (extra tokens after the capacity), which stay
+    untouched."""
     T = U.torch()
-    spec = _spec(name="strided", src_tokens=100, batch=2)
+    spec = _sized(_spec(name="strided", src_tokens=100, batch=2), kernel, 16)
     prob = S.make_problem(spec)
-    print(f"[edges] {spec.name}", flush=True)
+    print(f"[edges] {spec.name} {kernel}", flush=True)
     dev = U.DevProblem(prob)
+    assert U.small_kernel(prob, kvx.KVX_PREC_BF16X2) == (kernel == "small")
     pad = 24
     Ls, B, Hs, Ts, Ds = prob.src_k.shape
     big_k = T.full((Ls, B, Hs, Ts + pad, Ds), float("nan"), dtype=T.bfloat16, device="cuda")
@@ -178,6 +205,15 @@ def test_strided_source_view():
     T.cuda.synchronize()
     rk, rv = O.translate(prob, cap=dev.cap)
     U.check_full(dev, rk, rv, spec.name)
+    Lt, _, Ht, cap, Dt = dev.tgt_k.shape
+    out_k = T.full((Lt, B, Ht, cap + pad, Dt), float("nan"), dtype=T.bfloat16, device="cuda")
+    out_v = T.full_like(out_k, float("nan"))
+    dev.tr(dev.src_k, dev.src_v, out_k, out_v, cap,
+           tgt_stride=tuple(int(x) for x in out_k.stride()[:4]))
+    T.cuda.synchronize()
+    for out, ref in ((out_k, dev.tgt_k), (out_v, dev.tgt_v)):
+        assert T.equal(out[:, :, :, :cap], ref)
+        assert T.isnan(out[:, :, :, cap:]).all()
     dev.close()
 
 
@@ -198,7 +234,10 @@ def test_misaligned_layout_refused():
 
 # (source heads x dim, target heads x dim, mix, tokens, batch, largest span, precision, random map)
 RESIDENT = [
-    ((2, 64), (3, 128), 1, 130, 1, 1, kvx.KVX_PREC_BF16X2, False),    # one chunk, single entries
+    ((2, 64), (3, 128), 1, 130, 1, 1, kvx.KVX_PREC_BF16X2, False),    # a small call
+    ((2, 64), (3, 128), 1, 130, 8, 1, kvx.KVX_PREC_BF16X2, False),    # one chunk, single entries
+    ((1, 128), (6, 128), 1, 1500, 4, 4, kvx.KVX_PREC_BF16X2, False),  # one chunk, ranges within groups
+    ((4, 32), (6, 128), 1, 1100, 5, 3, kvx.KVX_PREC_F16, True),
     ((2, 128), (8, 64), 1, 517, 5, 5, kvx.KVX_PREC_BF16X2, False),    # fourth and fifth entries
     ((1, 256), (2, 256), 1, 640, 4, 4, kvx.KVX_PREC_BF16X2, False),   # no rotation table (Ds 256)
     ((1, 64), (4, 128), 4, 900, 4, 3, kvx.KVX_PREC_F16, False),       # four mixed layers in a row
@@ -234,6 +273,7 @@ def test_resident_transform(case):
         marks = (S.outlier_channels(spec, 0), S.outlier_channels(spec, 1))
     dev = U.DevProblem(prob, prec, cap=int(prob.tgt_tokens.max()), outliers=marks)
     assert dev.tr.info().kernel == 1 and dev.tr.info().tile_order == 2
+    assert U.small_kernel(prob, prec) == (batch == 1)
     dev.run()
     U.torch().cuda.synchronize()
     rk, rv = O.translate(prob, cap=dev.cap)

@@ -48,9 +48,22 @@ def _same(a, b):
     assert T.equal(a.view(T.int16), b.view(T.int16))
 
 
+# the call's size selects the small-call kernel or the persistent one
+KERNELS = pytest.mark.parametrize("kernel", ["small", "persistent"])
+
+
+def _sized(spec, kernel):
+    spec = spec if kernel == "small" else U.more_layers(spec, 13)
+    for prec in (kvx.KVX_PREC_BF16X2_OUTLIER, kvx.KVX_PREC_BF16):
+        assert U.small_kernel(S.make_problem(spec), prec) == (kernel == "small")
+    return spec
+
+
+@KERNELS
 @pytest.mark.parametrize("spans", [False, True])
-def test_no_marks_is_bf16_and_all_marks_is_bf16x2(spans):
-    spec = _spec(name=f"outlier-extremes-{spans}", **({"span_lo": 1, "span_hi": 3} if spans else {}))
+def test_no_marks_is_bf16_and_all_marks_is_bf16x2(spans, kernel):
+    spec = _sized(_spec(name=f"outlier-extremes-{spans}",
+                        **({"span_lo": 1, "span_hi": 3} if spans else {})), kernel)
     prob = S.make_problem(spec)
     shape = (spec.src.n_layers, spec.src.n_kv_heads, spec.src.head_dim)
     none = (np.zeros(shape, bool), np.zeros(shape, bool))
@@ -73,14 +86,15 @@ def test_no_marks_is_bf16_and_all_marks_is_bf16x2(spans):
     ref.close()
 
 
+@KERNELS
 @pytest.mark.parametrize("kw", [
     {},
     {"span_lo": 1, "span_hi": 3},
     {"src": S.ModelShape(4, 2, 64, 1.0e4), "tgt": S.ModelShape(2, 3, 128, 1.0e6), "mix": 2,
      "layer_map": (0, 1, 3, 2), "span_lo": 1, "span_hi": 2},
 ], ids=["ident", "spans", "ds64-mix2"])
-def test_marked_outliers_parity(kw):
-    spec = _spec(name="outlier-parity", **kw)
+def test_marked_outliers_parity(kw, kernel):
+    spec = _sized(_spec(name="outlier-parity", **kw), kernel)
     prob = S.make_problem(spec)
     dev = _run(prob, kvx.KVX_PREC_BF16X2_OUTLIER, _marks(spec))
     info = dev.tr.info()

@@ -37,13 +37,28 @@ def _bits(t):
     return t.view(T.int16).clone()
 
 
+# the call's size selects the small-call kernel or the persistent one
+KERNELS = pytest.mark.parametrize("kernel", ["small", "persistent"])
+
+
+def _sized(spec, kernel):
+    return spec if kernel == "small" else U.more_layers(spec, 13)
+
+
+def _runs(prob, kernel):
+    return U.small_kernel(prob, kvx.KVX_PREC_BF16X2) == (kernel == "small")
+
+
+@KERNELS
 @pytest.mark.parametrize("spans", [False, True])
-def test_graph_capture_replays(spans):
+def test_graph_capture_replays(spans, kernel):
     assert os.environ.get("KVX_VALIDATE", "0") != "1"
     T = U.torch()
-    spec = _spec(name=f"graph-{spans}", **({"span_lo": 1, "span_hi": 3} if spans else {}))
+    spec = _sized(_spec(name=f"graph-{spans}", **({"span_lo": 1, "span_hi": 3} if spans else {})),
+                  kernel)
     prob = S.make_problem(spec)
-    print(f"[streams] {spec.name}", flush=True)
+    assert _runs(prob, kernel)
+    print(f"[streams] {spec.name} {kernel}", flush=True)
     dev = U.DevProblem(prob, cap=max(1, int(prob.tgt_tokens.max())))
     dev.run()
     T.cuda.synchronize()
@@ -70,10 +85,12 @@ def test_graph_capture_replays(spans):
     dev.close()
 
 
-def test_two_streams_concurrent():
+@KERNELS
+def test_two_streams_concurrent(kernel):
     T = U.torch()
-    a = U.DevProblem(S.make_problem(_spec(name="stream-a", span_lo=1, span_hi=3)))
-    b = U.DevProblem(S.make_problem(_spec(name="stream-b", seed=11, src_tokens=520)))
+    a = U.DevProblem(S.make_problem(_sized(_spec(name="stream-a", span_lo=1, span_hi=3), kernel)))
+    b = U.DevProblem(S.make_problem(_sized(_spec(name="stream-b", seed=11, src_tokens=520), kernel)))
+    assert _runs(a.prob, kernel) and _runs(b.prob, kernel)
     print("[streams] eager references", flush=True)
     a.run()
     b.run()
