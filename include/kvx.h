@@ -156,8 +156,9 @@ typedef struct kvx_plan kvx_plan;
  * Errors: KVX_EINVAL (NULL/out of range), KVX_ESHAPE, KVX_EUNSUPPORTED
  * (head_dim odd; or a plan the matrix-core kernel does not tile -- fp32, or
  * head_dim not a multiple of 16 (source) / 64 (target) or above 512 -- whose
- * contraction length mix*Hs*Ds exceeds 16384, the pooled rows the general
- * kernel keeps in LDS), KVX_ENOMEM, KVX_EHIP.  On error *out is set to NULL. */
+ * contraction length mix*Hs*Ds exceeds 16384, a fixed limit of the interface
+ * that the kernel itself does not need), KVX_ENOMEM, KVX_EHIP.  On error *out
+ * is set to NULL. */
 kvx_status kvx_plan_create(const kvx_plan_desc* desc, kvx_plan** out);
 
 /* Enqueue the translation on `stream` (a hipStream_t; NULL = default stream).
@@ -223,9 +224,12 @@ const char* kvx_status_string(kvx_status s);
 /* Last HIP error code seen by this thread (0 if none). */
 int32_t kvx_last_hip_error(void);
 
-/* Which kernel a plan dispatches to and its launch shape (diagnostics). */
+/* Which kernel a plan dispatches to and its launch shape (diagnostics).
+ * tile_rows, tile_cols, threads and tile_order describe the kernel of large
+ * calls; calls of few rows run one of other tiles (the same bits with kernel 1,
+ * fp32 sums in another order with kernel 0). */
 typedef struct {
-  int32_t kernel;        /* 0 = fp32 tiled kernel, 1 = bf16 MFMA fused kernel */
+  int32_t kernel;        /* 0 = general kernel, fp32 arithmetic; 1 = bf16 MFMA fused kernel */
   int32_t tile_rows;     /* target rows per workgroup */
   int32_t tile_cols;     /* output features per workgroup */
   int32_t threads;       /* threads per workgroup */
@@ -243,7 +247,7 @@ typedef struct {
    * L2), chosen when din >= 1024; 2 = resident (for span maps: a row tile's
    * pooled, de-rotated rows are formed once and kept in LDS for all of its
    * N tiles), chosen when din <= 256 and dout > 256 -- identity-aligned
-   * calls of such a plan use 0.  0 for the tiled kernel. */
+   * calls of such a plan use 0.  0 for the general kernel. */
   int32_t tile_order;
 } kvx_plan_info;
 

@@ -16,8 +16,9 @@
 // product is taken as U = Z W^T, so a lane holds one output feature pair of 16
 // tokens.
 // Measured per call, the persistent kernel's time in brackets: 28 layers
-// [512 -> 256], 16 tokens 11.4 us [21.9], 128 tokens 14.1 us [22.2]; 28 layers
-// [3072 -> 512], spans of 1-2, 128 tokens 64 us [118].
+// [512 -> 256], 16 tokens 10.8 us [21.9], 128 tokens 13.3 us [22.2]; 28 layers
+// [3072 -> 512], spans of 1-2, 128 tokens 64 us [121]; with the caches flushed
+// before each call 26 us [35], 25 us [32] and 111 us [144].
 #pragma once
 
 #include "kernel_mfma.h"

@@ -111,7 +111,8 @@ bool fused_supported(const kvx_plan& p) {
          int64_t(p.tgt.n_layers) * p.mix <= kMaxLayerMap;
 }
 
-// Contractions the general kernel takes.
+// Contractions the general path takes (a fixed limit of the interface; the row
+// kernel's own is far below it, the general kernel has none).
 constexpr int kMaxTiledDin = 16384;
 
 // Pair blocks (32 output RoPE pairs) and chunks (64 input RoPE pairs) of the
